@@ -15,7 +15,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspz.so")
-SOURCES = ["api.hip", "kernels.hip", "gemm.hip", "gemm_big.hip", "testing.hip"]
+SOURCES = ["api.hip", "kernels.hip", "rows.hip", "gemm.hip", "gemm_big.hip", "testing.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -32,7 +32,7 @@
 #include <mutex>
 #include <new>
 
-#include "kernels.h"
+#include "rows.h"
 
 using namespace spz;
 
@@ -170,6 +170,27 @@ struct spz_ctx {
   // part's workspace and one launch at the end of the part reduces them all.
   struct RedQueue { float* base = nullptr; int64_t cap = 0, off = 0; double bytes = 0.0; ReduceJobs jobs{}; };
   RedQueue red[2];
+  // Row-tile path (rows.h): available when the networks fit it; whether the layer-by-layer
+  // path's buffers exist; which of the two the current batch takes; what the last step took.
+  struct RowPlan {   // one per tile height (index tm - 1)
+    RowOp* ops = nullptr;
+    int n_crit = 0, n_act = 0, n_sampler = 0;   // consecutive in ops
+    int max_blocks = 0;
+    RowArgs lay{};     // LDS layout
+    size_t lds = 0;
+  };
+  RowPlan rplan[2];
+  bool rows_ok = false, layers_ok = false, rows_on = false, last_rows = false;
+  int rows_nets = 2;             // nets per operation where both critics run
+  void *xpk = nullptr, *dzh_pk = nullptr;
+  std::vector<void*> hpk[3], dzpk[3];      // per net and hidden layer: packed activations and gradients
+  std::vector<float*> bpart[3];            // per net and layer: bias-gradient partials
+  float* wpart_out[3] = {nullptr, nullptr, nullptr};   // critics: output weight partials
+  void *PF = nullptr, *PT = nullptr, *TF = nullptr;    // packed weight images
+  float* wg_part = nullptr;                // weight-gradient slices
+  int64_t wg_cap = 0;
+  RowPBlk* pblk = nullptr;                 // reduction + Adam work list: critics, then actor, then log(alpha)
+  int n_pblk_crit = 0, n_pblk_act = 0;
   // streams
   hipStream_t sc = nullptr, sa = nullptr;
   hipEvent_t ev_fork = nullptr, ev_c = nullptr, ev_a = nullptr;
@@ -910,10 +931,468 @@ hipError_t actor_part(spz_ctx* c, hipStream_t s) {
   return red_flush(c, 1, s);
 }
 
-// Adam (+ Polyak) over the parameter arena. critics / actor select the optimizer
-// ranges of this launch; step_add is 1 when the step counter has not been advanced
-// by k_finish yet.
-hipError_t adam(spz_ctx* c, bool critics, bool actor_step, bool actor, int step_add, hipStream_t s) {
+// ---------------------------------------------------------------------------------- row-tile path
+constexpr size_t ROW_LDS_MAX = 160 * 1024;
+
+int row_vec(const spz_ctx* c) { return c->bf16 ? 8 : 4; }
+int row_ks(const spz_ctx* c) { return c->bf16 ? 16 : 8; }
+size_t align16z(size_t x) { return (x + 15) / 16 * 16; }
+
+// LDS layout of a tile of 32 tm rows with `nets` critics side by side; returns its bytes.
+size_t row_layout(const spz_ctx* c, int tm, int nets, RowArgs& g) {
+  const int bm = 32 * tm, pa = c->net[0].L.back().out_p, nh = (int)c->hidden.size();
+  const size_t e = es(c);
+  g.tm = tm;
+  g.ldx = c->Kc + row_vec(c);
+  g.ldh = std::max(c->hmax, pa) + row_vec(c);
+  g.hnet = bm * g.ldh;
+  g.zp = std::max(pa, c->Ap) + 1;
+  size_t off = 0;
+  g.oX = 0;
+  off += align16z((size_t)bm * g.ldx * e);
+  g.oH = (int)off;
+  off += align16z((size_t)nets * g.hnet * e);
+  g.oZ = (int)off;   // actor output [bm, pa], or the two action gradients [bm, Ap]
+  off += align16z((size_t)std::max(bm * g.zp, c->td3 ? 0 : 2 * bm * g.zp) * 4);
+  g.oV = (int)off;
+  off += (size_t)6 * bm * 4;
+  g.oM = (int)off;   // mask bits: actor layers, then each layer of both critics
+  for (int l = 0; l < nh; ++l) off += (size_t)3 * bm * pad32(c->hidden[l]) / 8;
+  g.A = c->A; g.Ka = c->Ka; g.Ap = c->Ap; g.Kc = c->Kc; g.pa = pa; g.O = c->O; g.sac = c->td3 ? 0 : 1;
+  return off;
+}
+
+// Blocks per wave of the widest operation.
+int row_blocks(const spz_ctx* c, int nets) {
+  int m = (c->net[0].L.back().out_p / 32 + ROW_WAVES - 1) / ROW_WAVES;
+  const int wpn = ROW_WAVES / nets;
+  for (int h : c->hidden) m = std::max({m, (pad32(h) / 32 + wpn - 1) / wpn, (pad32(h) / 32 + ROW_WAVES - 1) / ROW_WAVES});
+  return std::max(m, (c->Ap / 32 + wpn - 1) / wpn);
+}
+
+// Whether the networks fit the row-tile path (sets rows_nets: both critics side by side, or
+// one after the other where LDS or the blocks per wave do not allow it). Policy heads of up to
+// 64 outputs, as for the head fused into the output product.
+constexpr int ROW_MAX_WIDTH = 512;
+bool row_fits(spz_ctx* c) {
+  if (c->net[0].L.back().out_p > 64 || c->hmax > ROW_MAX_WIDTH) return false;
+  for (int nets = 2; nets >= 1; --nets) {
+    RowArgs g{};
+    if (row_blocks(c, nets) <= ROW_MAX_BLOCKS && row_layout(c, 1, nets, g) <= ROW_LDS_MAX) {
+      c->rows_nets = nets;
+      return true;
+    }
+  }
+  return false;
+}
+
+// SAC networks whose layers all have mask bits (bf16, 128-multiple widths) keep the
+// layer-by-layer path, with its row split and one timing record per product, below this
+// batch: observers of small runs (spz_profile_*) see there what they always saw. The row-tile
+// path is the faster one on both sides of the line (256-128 bf16 at 500 rows: about a third).
+constexpr int ROW_MIN_SPLIT_BATCH = 1024;
+bool row_batch(const spz_ctx* c, int batch) {
+  if (!c->rows_ok) return false;
+  if (!c->bf16 || c->td3) return true;
+  for (int h : c->hidden)
+    if (pad32(h) % 128) return true;
+  return batch >= ROW_MIN_SPLIT_BATCH;
+}
+
+// Rows per tile (in units of 32) for a batch.
+int row_tm(const spz_ctx* c, int batch) {
+  return c->bf16 && c->rplan[1].ops && (batch + 63) / 64 >= 256 ? 2 : 1;
+}
+
+// The operations of the critic part, the actor part and the sampler-action call.
+struct RowBuilder {
+  spz_ctx* c;
+  int tm, nets;
+  std::vector<RowOp> v;
+  int nh, nl;
+  int mask_at(int ni, int l) const {   // u16 index of layer l's mask bits
+    int o = 0;
+    for (int i = 0; i < nh; ++i) {
+      const int n = pad32(c->hidden[i]) * tm * 2;   // 32-column blocks x tm x 64 lanes
+      if (i == l && ni == 0) return o;
+      o += n;
+    }
+    for (int i = 0; i < l; ++i) o += 2 * pad32(c->hidden[i]) * tm * 2;
+    return o + (ni == 2 ? pad32(c->hidden[l]) * tm * 2 : 0);
+  }
+  RowOp op(int kind) const {
+    RowOp o{};
+    o.kind = kind;
+    o.nets = 1;
+    o.mask = -1;
+    return o;
+  }
+  const void* pk(const void* base, int64_t off) const { return elem(c, base, off); }
+  // Layers of nets ni .. ni + n - 1 (target: target parameters) from X; hidden layers keep
+  // mask bits and packed images when asked.
+  void forward(int ni, int n, bool target, bool masks, bool packs) {
+    const int ks = row_ks(c);
+    const int last = ni == 0 ? nl : nl - 1;
+    for (int l = 0; l < last; ++l) {
+      const Lay& L = c->net[ni].L[l];
+      RowOp o = op(l == nl - 1 ? ROW_Z : ROW_HIDDEN);
+      o.net0 = ni; o.nets = n; o.nblk = L.out_p / 32; o.steps = L.in_p / ks; o.from_h = l > 0;
+      if (l < nl - 1 && masks) o.mask = mask_at(ni, l);
+      for (int k = 0; k < n; ++k) {
+        const Lay& Lk = c->net[ni + k].L[l];
+        o.w[k] = pk(target ? c->TF : c->PF, Lk.w);
+        o.bias[k] = wf(c, target, Lk.b);
+        if (l < nl - 1 && packs) o.pack[k] = c->hpk[ni + k][l];
+      }
+      v.push_back(o);
+    }
+    if (ni == 0) return;
+    const Lay& L = c->net[ni].L[nl - 1];
+    RowOp o = op(ROW_DOT);
+    o.net0 = ni; o.nets = n; o.nblk = L.in_p / 32;
+    for (int k = 0; k < n; ++k) {
+      o.w[k] = wf(c, target, c->net[ni + k].L[nl - 1].w);
+      o.bias[k] = wf(c, target, c->net[ni + k].L[nl - 1].b);
+    }
+    v.push_back(o);
+  }
+  void critics(bool target, bool masks, bool packs, int count) {
+    for (int ni = 1; ni <= count; ni += nets) forward(ni, std::min(nets, count), target, masks, packs);
+  }
+  // From dq to the gradient of the first hidden layer (grads: the critics' own gradients).
+  void critic_back(int ni, int n, bool grads) {
+    RowOp o = op(ROW_DZ);
+    const Lay& H = c->net[ni].L[nl - 1];
+    o.net0 = ni; o.nets = n; o.nblk = H.in_p / 32; o.mask = mask_at(ni, nl - 2);
+    for (int k = 0; k < n; ++k) {
+      o.w[k] = wf(c, false, c->net[ni + k].L[nl - 1].w);
+      if (!grads) continue;
+      o.pack[k] = c->dzpk[ni + k][nl - 2];
+      o.part[k] = c->bpart[ni + k][nl - 2];
+      o.wpart[k] = c->wpart_out[ni + k];
+      o.hpack[k] = c->hpk[ni + k][nl - 2];
+    }
+    v.push_back(o);
+    for (int l = nl - 2; l >= 1; --l) dgrad(ni, n, l, grads);
+  }
+  void dgrad(int ni, int n, int l, bool grads) {
+    const Lay& L = c->net[ni].L[l];
+    RowOp o = op(ROW_DGRAD);
+    o.net0 = ni; o.nets = n; o.nblk = L.in_p / 32; o.steps = L.out_p / row_ks(c); o.from_h = 1;
+    o.mask = mask_at(ni, l - 1);
+    for (int k = 0; k < n; ++k) {
+      o.w[k] = pk(c->PT, c->net[ni + k].L[l].w);
+      if (!grads) continue;
+      o.pack[k] = c->dzpk[ni + k][l - 1];
+      o.part[k] = c->bpart[ni + k][l - 1];
+    }
+    v.push_back(o);
+  }
+  void load(bool xsa, bool pack) {
+    RowOp o = op(ROW_LOAD);
+    o.flags = xsa;
+    if (pack) o.pack[0] = c->xpk;
+    v.push_back(o);
+  }
+  void head(bool policy) {
+    RowOp o = op(ROW_HEAD);
+    o.flags = policy;
+    v.push_back(o);
+  }
+  void critic_part() {
+    load(false, false);
+    forward(0, 1, c->td3, false, false);
+    head(false);
+    critics(true, false, false, 2);
+    v.push_back(op(ROW_TARGET));
+    load(true, true);
+    critics(false, true, true, 2);
+    RowOp o = op(ROW_CLOSS);
+    for (int k = 0; k < 2; ++k) o.part[k] = c->bpart[1 + k][nl - 1];
+    v.push_back(o);
+    for (int ni = 1; ni <= 2; ni += nets) critic_back(ni, nets, true);
+  }
+  void actor_part() {
+    const int n = c->td3 ? 1 : 2;
+    load(true, false);
+    forward(0, 1, false, true, true);
+    head(true);
+    critics(false, true, false, n);
+    v.push_back(op(ROW_ALOSS));
+    for (int ni = 1; ni <= n; ni += nets) {
+      const int m = std::min(nets, n);
+      critic_back(ni, m, false);
+      RowOp o = op(ROW_DACT);
+      const Lay& L = c->net[ni].L[0];
+      o.net0 = ni; o.nets = m; o.nblk = c->Ap / 32; o.steps = L.out_p / row_ks(c); o.from_h = 1;
+      for (int k = 0; k < m; ++k) o.w[k] = pk(c->PT, c->net[ni + k].L[0].w);
+      v.push_back(o);
+    }
+    RowOp o = op(ROW_HEAD_BWD);
+    o.nblk = c->net[0].L.back().out_p / 32;
+    o.pack[0] = c->dzh_pk;
+    o.part[0] = c->bpart[0][nl - 1];
+    v.push_back(o);
+    for (int l = nl - 1; l >= 1; --l) dgrad(0, 1, l, true);
+  }
+  void sampler() {
+    v.push_back(op(ROW_OBS));
+    forward(0, 1, false, false, false);
+    v.push_back(op(ROW_ACT));
+  }
+};
+
+// Weight-gradient products of a part (0: critics, 1: actor) in work-list order.
+struct RowWLayer { int ni, l; };
+std::vector<RowWLayer> row_wlayers(const spz_ctx* c, int part) {
+  std::vector<RowWLayer> v;
+  const int nl = (int)c->net[0].L.size();
+  for (int ni = part ? 0 : 1; ni <= (part ? 0 : 2); ++ni)
+    for (int l = 0; l < (part ? nl : nl - 1); ++l) v.push_back({ni, l});
+  return v;
+}
+
+// Slices the batch of a launch's weight gradients is split into: enough waves for the chip
+// and at least ROW_MIN_GROUPS row groups each.
+constexpr int ROW_TARGET_WAVES = 1024, ROW_MIN_GROUPS = 4;
+int row_slices(int tiles, int groups) {
+  return std::max(1, std::min(ROW_TARGET_WAVES / std::max(tiles, 1), groups / ROW_MIN_GROUPS));
+}
+int row_tiles(const spz_ctx* c, bool crit, bool act) {
+  int t = 0;
+  for (int part = 0; part < 2; ++part)
+    if (part ? act : crit)
+      for (const RowWLayer& w : row_wlayers(c, part)) {
+        const Lay& L = c->net[w.ni].L[w.l];
+        t += row_wjob_tiles(L.out_p / 32, L.in_p / 32);
+      }
+  return t;
+}
+
+// Rebuilds the packed weight images from P and T.
+hipError_t refresh_packed(spz_ctx* c, hipStream_t s) {
+  if (!c->rows_ok) return hipSuccess;
+  RowPArgs p{};
+  p.a.P = c->P; p.a.T = c->T;
+  p.blk = c->pblk;
+  p.first = 0;
+  p.count = c->n_pblk_crit + c->n_pblk_act;
+  p.PF = c->PF; p.PT = c->PT; p.TF = c->TF;
+  return launch_row_adam(c->bf16, p, s);
+}
+
+int setup_rows(spz_ctx* c) {
+  const size_t e = es(c);
+  const int64_t Bp = c->Bp;
+  const int nh = (int)c->hidden.size(), nl = nh + 1;
+  const int pa = c->net[0].L.back().out_p;
+  const size_t nt = (size_t)Bp / 32;   // the most tiles
+  CK(dalloc(c, &c->PF, (size_t)c->n_arena * e));
+  CK(dalloc(c, &c->PT, (size_t)c->n_arena * e));
+  CK(dalloc(c, &c->TF, (size_t)c->n_arena * e));
+  CK(dalloc(c, &c->xpk, (size_t)Bp * c->Kc * e));
+  CK(dalloc(c, &c->dzh_pk, (size_t)Bp * pa * e));
+  for (int ni = 0; ni < 3; ++ni) {
+    c->hpk[ni].assign(nh, nullptr);
+    c->dzpk[ni].assign(nh, nullptr);
+    c->bpart[ni].assign(nl, nullptr);
+    for (int l = 0; l < nh; ++l) {
+      const size_t b = (size_t)Bp * pad32(c->hidden[l]) * e;
+      CK(dalloc(c, &c->hpk[ni][l], b));
+      CK(dalloc(c, &c->dzpk[ni][l], b));
+    }
+    for (int l = 0; l < nl; ++l) CK(dalloc_t(c, &c->bpart[ni][l], nt * c->net[ni].L[l].out_p * 4));
+    if (ni) CK(dalloc_t(c, &c->wpart_out[ni], nt * c->net[ni].L[nl - 1].in_p * 4));
+  }
+  // Weight-gradient slices: a step's launches use the workspace one after the other; slice
+  // counts grow with the batch and with fewer products in the launch.
+  const int groups = (int)(Bp / row_ks(c));
+  for (int part = 0; part < 2; ++part) {
+    const int slices = row_slices(row_tiles(c, part == 0, part == 1), groups);
+    int64_t n = 0;
+    for (const RowWLayer& w : row_wlayers(c, part)) {
+      const Lay& L = c->net[w.ni].L[w.l];
+      n += (int64_t)slices * L.out_p * L.in_p;
+    }
+    c->wg_cap += n;
+  }
+  CK(dalloc_t(c, &c->wg_part, (size_t)c->wg_cap * 4));
+  // reduction + Adam work list
+  std::vector<RowPBlk> blk;
+  const size_t n_crit_jobs = row_wlayers(c, 0).size();
+  for (int part = 0; part < 2; ++part) {
+    const std::vector<RowWLayer> wl = row_wlayers(c, part);
+    for (size_t j = 0; j < wl.size(); ++j) {
+      const Lay& L = c->net[wl[j].ni].L[wl[j].l];
+      const int mb = L.out_p / 32, nb = L.in_p / 32, fs = L.in_p / row_ks(c), ts = L.out_p / row_ks(c);
+      // transposed images: every layer but the first; of a critic's first layer the action block
+      const int t0 = wl[j].l > 0 ? 0 : (wl[j].ni ? c->Ka / 32 : nb);
+      for (int m = 0; m < mb; ++m)
+        for (int n = 0; n < nb; ++n) {
+          RowPBlk b{};
+          b.net = wl[j].ni;
+          b.off = L.w + (int64_t)m * 32 * L.in_p + n * 32;
+          b.ld = L.in_p;
+          b.job = (int)(j + (part ? n_crit_jobs : 0));
+          b.blk = m * nb + n;
+          const int64_t frag = 64 * row_vec(c), per = 32 / row_ks(c);
+          b.fwd = L.w + ((int64_t)m * fs + n * per) * frag;
+          b.tr = n >= t0 ? L.w + ((int64_t)(n - t0) * ts + m * per) * frag : -1;
+          blk.push_back(b);
+        }
+    }
+    auto vec = [&](int ni, int64_t off, const float* p, int n) {
+      for (int i = 0; i < n; i += 16) {
+        RowPBlk b{};
+        b.kind = 1; b.net = ni; b.off = off + i; b.ld = n; b.part = p + i;
+        blk.push_back(b);
+      }
+    };
+    for (int ni = part ? 0 : 1; ni <= (part ? 0 : 2); ++ni) {
+      for (int l = 0; l < (part ? nl : nl - 1); ++l) vec(ni, c->net[ni].L[l].b, c->bpart[ni][l], c->net[ni].L[l].out_p);
+      if (!part) {
+        const Lay& H = c->net[ni].L[nl - 1];
+        vec(ni, H.w, c->wpart_out[ni], H.in_p);
+        RowPBlk b{};
+        b.kind = 2; b.net = ni; b.off = H.b; b.part = c->bpart[ni][nl - 1];
+        blk.push_back(b);
+      }
+    }
+    if (part == 0) {
+      c->n_pblk_crit = (int)blk.size();
+    } else {
+      RowPBlk b{};
+      b.kind = 3; b.off = c->la;
+      blk.push_back(b);
+      c->n_pblk_act = (int)blk.size() - c->n_pblk_crit;
+    }
+  }
+  CK(dalloc_t(c, &c->pblk, blk.size() * sizeof(RowPBlk)));
+  CK(hipMemcpy(c->pblk, blk.data(), blk.size() * sizeof(RowPBlk), hipMemcpyHostToDevice));
+  // operation lists
+  for (int tm = 1; tm <= (c->bf16 ? 2 : 1); ++tm) {
+    spz_ctx::RowPlan& P = c->rplan[tm - 1];
+    P.lds = row_layout(c, tm, c->rows_nets, P.lay);
+    if (P.lds > ROW_LDS_MAX) continue;
+    RowBuilder b{c, tm, c->rows_nets, {}, nh, nl};
+    b.critic_part();
+    P.n_crit = (int)b.v.size();
+    b.actor_part();
+    P.n_act = (int)b.v.size() - P.n_crit;
+    b.sampler();
+    P.n_sampler = (int)b.v.size() - P.n_crit - P.n_act;
+    P.max_blocks = row_blocks(c, c->rows_nets);
+    CK(dalloc_t(c, &P.ops, b.v.size() * sizeof(RowOp)));
+    CK(hipMemcpy(P.ops, b.v.data(), b.v.size() * sizeof(RowOp), hipMemcpyHostToDevice));
+  }
+  return SPZ_OK;
+}
+
+// The halves of a step on the row-tile path: activations, losses and output gradients of
+// both (or one) in one launch.
+hipError_t row_step(spz_ctx* c, bool crit, bool act, hipStream_t s) {
+  const int tm = row_tm(c, c->B);
+  const spz_ctx::RowPlan& P = c->rplan[tm - 1];
+  RowArgs g = P.lay;
+  g.ops = P.ops;
+  g.tiles = (c->B + 32 * tm - 1) / (32 * tm);
+  g.parts = (crit ? 1 : 0) + (act ? 1 : 0);
+  int i = 0;
+  if (crit) { g.op0[i] = 0; g.nops[i++] = P.n_crit; }
+  if (act) { g.op0[i] = P.n_crit; g.nops[i++] = P.n_act; }
+  g.B = c->B;
+  g.seed = c->seed; g.step = c->d_step;
+  g.xsa = c->xsa; g.xs2 = c->xs2; g.r = c->r; g.d = c->d; g.log_alpha = log_alpha_ptr(c);
+  g.gamma = c->hp.gamma; g.lmin = c->hp.log_std_min; g.lmax = c->hp.log_std_max;
+  g.noise = c->hp.policy_noise; g.clip = c->hp.noise_clip;
+  g.y = c->y; g.q1 = c->q1; g.q2 = c->q2; g.qp1 = c->qp1; g.qp2 = c->qp2; g.logp = c->logp;
+  g.th = c->th; g.se = c->se; g.lm = c->lm; g.da = c->da1;
+  g.cpart = c->c_lpart; g.apart = c->a_lpart;
+  // Products of the part's rows (work done, and a first-order count of the operand bytes).
+  double macs = 0.0;
+  auto fw = [&](int ni) { double m = 0.0; for (const Lay& L : c->net[ni].L) m += (double)L.in_p * L.out_p; return m; };
+  auto bw = [&](int ni) { double m = 0.0; for (size_t l = 1; l < c->net[ni].L.size(); ++l) m += (double)c->net[ni].L[l].in_p * c->net[ni].L[l].out_p; return m; };
+  if (crit) macs += fw(0) + 4 * fw(1) + 2 * bw(1);
+  if (act) macs += fw(0) + bw(0) + (c->td3 ? 1 : 2) * (fw(1) + bw(1));
+  return timed(c, "row_step", g.tiles * 32 * tm, g.parts, c->hmax, 2.0 * c->B * macs, 0.0, s,
+               [&] { return launch_rows(c->bf16, g, P.max_blocks, P.lds, s); });
+}
+
+// Weight gradients of the critics and / or the actor, with the step's finish when asked;
+// then their reduction and Adam (+ Polyak, a) and the packed images.
+hipError_t row_update(spz_ctx* c, bool crit, bool act, const FinishArgs* fin, const AdamArgs& a, double adam_bytes,
+                      hipStream_t s) {
+  const int tm = row_tm(c, c->B), tiles = (c->B + 32 * tm - 1) / (32 * tm);
+  RowWArgs W{};
+  RowPArgs p{};
+  W.groups = tiles * 32 * tm / row_ks(c);
+  const int slices = row_slices(row_tiles(c, crit, act), W.groups);
+  int64_t off = 0;
+  int index = 0;   // of the product in the work list
+  double macs = 0.0;
+  for (int part = 0; part < 2; ++part)
+    for (const RowWLayer& w : row_wlayers(c, part)) {
+      const int at = index++;
+      if (!(part ? act : crit)) continue;
+      const Lay& L = c->net[w.ni].L[w.l];
+      RowWJob& j = W.j[W.n++];
+      j.a = w.l == (int)c->net[w.ni].L.size() - 1 ? c->dzh_pk : c->dzpk[w.ni][w.l];
+      j.b = w.l == 0 ? c->xpk : c->hpk[w.ni][w.l - 1];
+      j.mblk = L.out_p / 32;
+      j.nblk = L.in_p / 32;
+      j.bcb = w.l == 0 ? c->Kc / 32 : j.nblk;
+      j.slices = slices;
+      j.part = c->wg_part + off;
+      const int64_t n = (int64_t)L.out_p * L.in_p;
+      p.j[at] = RowPJob{j.part, n, slices};
+      off += n * slices;
+      macs += (double)n;
+    }
+  if (off > c->wg_cap) return hipErrorInvalidValue;
+  if (fin) {
+    W.has_fin = 1;
+    W.fin = *fin;
+  }
+  HK(timed(c, "row_wgrad", c->B, W.n, slices, 2.0 * c->B * macs, 0.0, s, [&] { return launch_row_wgrad(c->bf16, W, s); }));
+  p.a = a;
+  p.blk = c->pblk;
+  p.first = crit ? 0 : c->n_pblk_crit;
+  p.count = (crit ? c->n_pblk_crit : 0) + (act ? c->n_pblk_act : 0);
+  p.vslices = tiles;
+  p.PF = c->PF; p.PT = c->PT; p.TF = c->TF;
+  p.update = 1;
+  return timed(c, "row_adam", (int)c->n_arena, 0, (crit ? 2 : 0) + (act ? 1 : 0), 0.0, adam_bytes + 4.0 * off, s,
+               [&] { return launch_row_adam(c->bf16, p, s); });
+}
+
+// Sampler actions for n observation rows in device memory.
+hipError_t row_act(spz_ctx* c, const float* obs, int n, int64_t row0, bool stochastic, uint32_t counter, float* act,
+                   hipStream_t s) {
+  const int tm = row_tm(c, n);
+  const spz_ctx::RowPlan& P = c->rplan[tm - 1];
+  RowArgs g = P.lay;
+  g.ops = P.ops;
+  g.tiles = (n + 32 * tm - 1) / (32 * tm);
+  g.parts = 1;
+  g.op0[0] = P.n_crit + P.n_act;
+  g.nops[0] = P.n_sampler;
+  g.B = n;
+  g.seed = c->seed;
+  g.lmin = c->hp.log_std_min; g.lmax = c->hp.log_std_max;
+  g.obs = obs; g.act = act; g.stochastic = stochastic ? 1 : 0; g.counter = counter; g.row0 = row0;
+  return launch_rows(c->bf16, g, P.max_blocks, P.lds, s);
+}
+
+FinishArgs finish_args(const spz_ctx* c, int blocks, bool actor_step) {
+  return FinishArgs{c->c_lpart, c->a_lpart, blocks, blocks, c->B, c->td3 ? 0 : 1, actor_step ? 1 : 0,
+                    c->hp.learn_alpha, c->hp.target_entropy, log_alpha_ptr(c), c->td3 ? nullptr : c->G + c->la,
+                    c->rec, c->rec_cap, c->d_step};
+}
+
+// Arguments of Adam (+ Polyak) over the parameter arena. critics / actor select the
+// optimizer ranges; step_add is 1 when the step counter has not been advanced by the
+// finish yet. *bytes: what the pass must move.
+AdamArgs adam_args(const spz_ctx* c, bool critics, bool actor_step, bool actor, int step_add, double* bytes) {
   const Net& an = c->net[0];
   AdamArgs a{};
   a.P = c->P; a.M = c->M; a.V = c->V; a.T = c->T; a.G = c->G; a.Pb = c->Pb; a.Tb = c->Tb;
@@ -936,10 +1415,36 @@ hipError_t adam(spz_ctx* c, bool critics, bool actor_step, bool actor, int step_
   const double n_act = (double)(an.end - an.off);
   const double n_adam = (critics ? n_crit : 0.0) + (a.do_actor ? n_act : 0.0) + (a.do_alpha ? 1.0 : 0.0);
   const double n_pol = (a.polyak_critic ? n_crit : 0.0) + (a.polyak_actor ? n_act : 0.0);
-  const double bytes = 28.0 * n_adam + 8.0 * n_pol + (c->bf16 ? 2.0 * (n_adam + n_pol) : 0.0);
+  *bytes = 28.0 * n_adam + 8.0 * n_pol + (c->bf16 ? 2.0 * (n_adam + n_pol) : 0.0);
+  return a;
+}
+
+hipError_t adam(spz_ctx* c, bool critics, bool actor_step, bool actor, int step_add, hipStream_t s) {
+  double bytes = 0.0;
+  const AdamArgs a = adam_args(c, critics, actor_step, actor, step_add, &bytes);
   HK(timed(c, "adam_polyak", (int)c->n_arena, 0, (critics ? 2 : 0) + (actor ? 1 : 0), 0.0, bytes, s,
            [&] { return launch_adam(a, s); }));
   return refresh_wt(c, s);
+}
+
+// The step after the gather on the row-tile path, all on s0 (the two halves of a snapshot
+// step share a launch).
+hipError_t row_enqueue(spz_ctx* c, bool actor_step, bool sequential, hipStream_t s0) {
+  const int tm = row_tm(c, c->B), tiles = (c->B + 32 * tm - 1) / (32 * tm);
+  const FinishArgs f = finish_args(c, tiles, actor_step);
+  double bytes = 0.0;
+  if (!sequential) {
+    HK(row_step(c, true, actor_step, s0));
+    const AdamArgs a = adam_args(c, true, actor_step, true, 0, &bytes);
+    return row_update(c, true, actor_step, &f, a, bytes, s0);
+  }
+  HK(row_step(c, true, false, s0));
+  const AdamArgs ac = adam_args(c, true, actor_step, false, 1, &bytes);
+  HK(row_update(c, true, false, nullptr, ac, bytes, s0));
+  if (!actor_step) return timed(c, "finish", 0, 0, 0, 0.0, 0.0, s0, [&] { return launch_finish(f, s0); });
+  HK(row_step(c, false, true, s0));
+  const AdamArgs aa = adam_args(c, false, true, true, 0, &bytes);
+  return row_update(c, false, true, &f, aa, bytes, s0);
 }
 
 int enqueue_step(spz_ctx* c, hipStream_t s0) {
@@ -952,17 +1457,25 @@ int enqueue_step(spz_ctx* c, hipStream_t s0) {
     ~StepTiming() { c->pf_step = true; }
   } step_timing{c};
   c->pf_step = t % c->pf_stride == 0;
-  const bool two = c->hp.n_streams == 2 && !sequential;
+  const bool rows = c->rows_on;
+  const bool two = c->hp.n_streams == 2 && !sequential && !rows;
+  c->last_rows = rows;
   c->xs_act = two ? c->xsp : c->xsa;
+  // The row-tile path keeps the policy's actions in LDS: xsa holds the sampled ones.
   GatherArgs g{c->buf, c->row_bytes, c->off_a, c->off_s2, c->off_r, c->off_d, c->O, c->A, c->Ka, c->Kc,
                c->B, c->seed, (uint32_t)c->size, c->d_step, c->xsa, c->xs2, two ? c->xsp : nullptr, c->r, c->d,
-               c->idx, two ? nullptr : c->abuf};
+               c->idx, two || rows ? nullptr : c->abuf};
   {
     const double e = (double)es(c);
     // s to xsa (and xsp on two streams), s' to xs2; a to xsa (and abuf on one stream)
-    const double copies = two ? 3.0 : 2.0, acopies = two ? 1.0 : 2.0;
+    const double copies = two ? 3.0 : 2.0, acopies = two || rows ? 1.0 : 2.0;
     const double bytes = (double)c->B * ((2.0 * c->O + c->A) * e + 8.0 + (copies * c->O + acopies * c->A) * e + 12.0);
     CK(timed(c, "gather", c->B, c->O, c->A, 0.0, bytes, s0, [&] { return launch_gather(c->bf16, g, s0); }));
+  }
+  if (rows) {
+    CK(row_enqueue(c, actor_step, sequential, s0));
+    c->h_step = t;
+    return SPZ_OK;
   }
   hipStream_t sc = s0, sa = s0;
   if (two) {
@@ -985,9 +1498,7 @@ int enqueue_step(spz_ctx* c, hipStream_t s0) {
       CK(hipStreamWaitEvent(s0, c->ev_a, 0));
     }
   }
-  FinishArgs f{c->c_lpart, c->a_lpart, loss_blocks(c->Bp), loss_blocks(c->Bp), c->B, c->td3 ? 0 : 1,
-               actor_step ? 1 : 0, c->hp.learn_alpha, c->hp.target_entropy, log_alpha_ptr(c),
-               c->td3 ? nullptr : c->G + c->la, c->rec, c->rec_cap, c->d_step};
+  const FinishArgs f = finish_args(c, loss_blocks(c->Bp), actor_step);
   CK(timed(c, "finish", 0, 0, 0, 0.0, 0.0, s0, [&] { return launch_finish(f, s0); }));
   CK(adam(c, !sequential, actor_step, true, 0, s0));
   c->h_step = t;
@@ -1049,26 +1560,21 @@ int ctx_sync(spz_ctx* c) {
   return SPZ_OK;
 }
 
-int setup(spz_ctx* c) {
+// The operand images of P and T (every path's): after any change of the parameters but a
+// step's own Adam.
+hipError_t refresh_images(spz_ctx* c, hipStream_t s) {
+  HK(refresh_packed(c, s));
+  if (!c->Pb) return hipSuccess;
+  HK(launch_to_bf16(c->P, c->Pb, c->n_arena, s));
+  HK(launch_to_bf16(c->T, c->Tb, c->n_arena, s));
+  return refresh_wt(c, s);
+}
+
+// Operand images and workspaces of the layer-by-layer path.
+int setup_layers(spz_ctx* c) {
   const size_t e = es(c);
   const int64_t Bp = c->Bp;
   const int nh = (int)c->hidden.size();
-  // replay ring
-  // [obs | act | next_obs | rew done], each segment starting on a 16-byte boundary.
-  c->off_a = (int)align16((int64_t)c->O * e);
-  c->off_s2 = c->off_a + (int)align16((int64_t)c->A * e);
-  c->off_r = c->off_s2 + (int)align16((int64_t)c->O * e);
-  c->off_d = c->off_r + 4;
-  c->row_bytes = align16(c->off_d + 4);
-  c->cap = c->hp.capacity;
-  CK(dalloc_t(c, &c->buf, (size_t)(c->row_bytes * c->cap)));
-  // parameters
-  const size_t ab = (size_t)c->n_arena * 4;
-  CK(dalloc_t(c, &c->P, ab));
-  CK(dalloc_t(c, &c->G, ab));
-  CK(dalloc_t(c, &c->M, ab));
-  CK(dalloc_t(c, &c->V, ab));
-  CK(dalloc_t(c, &c->T, ab));
   if (c->bf16) {
     CK(dalloc_t(c, &c->Pb, (size_t)c->n_arena * 2));
     CK(dalloc_t(c, &c->Tb, (size_t)c->n_arena * 2));
@@ -1098,28 +1604,14 @@ int setup(spz_ctx* c) {
       CK(hipMemcpy(c->tjobs, jobs.data(), jobs.size() * sizeof(TransposeJob), hipMemcpyHostToDevice));
     }
   }
-  CK(dalloc_t(c, &c->d_step, 8));
-  CK(dalloc_t(c, &c->rec, (size_t)c->rec_cap * SPZ_REC_WIDTH * 4));
-  // batch
   const size_t xb = (size_t)Bp * c->Kc * e;
-  CK(dalloc(c, &c->xsa, xb));
-  CK(dalloc(c, &c->xs2, xb));
   CK(dalloc(c, &c->xsp, xb));
   CK(dalloc(c, &c->abuf, (size_t)Bp * c->A * e));
-  CK(dalloc_t(c, &c->r, Bp * 4));
-  CK(dalloc_t(c, &c->d, Bp * 4));
-  CK(dalloc_t(c, &c->idx, Bp * 4));
   const size_t hb = (size_t)Bp * c->hmax * e;
   const int pa = c->net[0].L.back().out_p;
-  float** f32s[] = {&c->logp2, &c->qt1, &c->qt2, &c->y, &c->q1, &c->q2, &c->dq1, &c->dq2,
-                    &c->logp, &c->qp1, &c->qp2, &c->dqp1, &c->dqp2};
-  for (float** p : f32s) CK(dalloc_t(c, p, Bp * 4));
+  for (float** p : {&c->logp2, &c->qt1, &c->qt2, &c->dq1, &c->dq2, &c->dqp1, &c->dqp2}) CK(dalloc_t(c, p, Bp * 4));
   CK(dalloc_t(c, &c->z2, (size_t)Bp * pa * 4));
   CK(dalloc_t(c, &c->z, (size_t)Bp * pa * 4));
-  CK(dalloc_t(c, &c->th, (size_t)Bp * c->A * 4));
-  CK(dalloc_t(c, &c->se, (size_t)Bp * c->A * 4));
-  CK(dalloc_t(c, &c->lm, (size_t)Bp * c->A * 4));
-  CK(dalloc_t(c, &c->da1, (size_t)Bp * c->Ap * 4));
   CK(dalloc_t(c, &c->da2, (size_t)Bp * c->Ap * 4));
   CK(dalloc(c, &c->dzh, (size_t)Bp * pa * e));
   for (int i = 0; i < 2; ++i) {
@@ -1186,8 +1678,56 @@ int setup(spz_ctx* c) {
     c->red[q].cap = red_need(c, q, (int)Bp);
     CK(dalloc_t(c, &c->red[q].base, (size_t)c->red[q].cap * 4));
   }
-  CK(dalloc_t(c, &c->c_lpart, (size_t)loss_blocks((int)Bp) * 3 * 8));
-  CK(dalloc_t(c, &c->a_lpart, (size_t)loss_blocks((int)Bp) * 2 * 8));
+  return SPZ_OK;
+}
+
+int setup(spz_ctx* c) {
+  const size_t e = es(c);
+  const int64_t Bp = c->Bp;
+  // replay ring
+  // [obs | act | next_obs | rew done], each segment starting on a 16-byte boundary.
+  c->off_a = (int)align16((int64_t)c->O * e);
+  c->off_s2 = c->off_a + (int)align16((int64_t)c->A * e);
+  c->off_r = c->off_s2 + (int)align16((int64_t)c->O * e);
+  c->off_d = c->off_r + 4;
+  c->row_bytes = align16(c->off_d + 4);
+  c->cap = c->hp.capacity;
+  CK(dalloc_t(c, &c->buf, (size_t)(c->row_bytes * c->cap)));
+  // parameters
+  const size_t ab = (size_t)c->n_arena * 4;
+  CK(dalloc_t(c, &c->P, ab));
+  CK(dalloc_t(c, &c->G, ab));
+  CK(dalloc_t(c, &c->M, ab));
+  CK(dalloc_t(c, &c->V, ab));
+  CK(dalloc_t(c, &c->T, ab));
+  CK(dalloc_t(c, &c->d_step, 8));
+  CK(dalloc_t(c, &c->rec, (size_t)c->rec_cap * SPZ_REC_WIDTH * 4));
+  // batch
+  const size_t xb = (size_t)Bp * c->Kc * e;
+  CK(dalloc(c, &c->xsa, xb));
+  CK(dalloc(c, &c->xs2, xb));
+  CK(dalloc_t(c, &c->r, Bp * 4));
+  CK(dalloc_t(c, &c->d, Bp * 4));
+  CK(dalloc_t(c, &c->idx, Bp * 4));
+  for (float** p : {&c->y, &c->q1, &c->q2, &c->logp, &c->qp1, &c->qp2}) CK(dalloc_t(c, p, Bp * 4));
+  CK(dalloc_t(c, &c->th, (size_t)Bp * c->A * 4));
+  CK(dalloc_t(c, &c->se, (size_t)Bp * c->A * 4));
+  CK(dalloc_t(c, &c->lm, (size_t)Bp * c->A * 4));
+  CK(dalloc_t(c, &c->da1, (size_t)Bp * c->Ap * 4));
+  c->rows_ok = row_fits(c);
+  c->layers_ok = !row_batch(c, 1);   // some batch size takes the layer-by-layer path
+  c->rows_on = row_batch(c, c->B);
+  if (c->rows_ok) {
+    const int rc = setup_rows(c);
+    if (rc) return rc;
+  }
+  if (c->layers_ok) {
+    const int rc = setup_layers(c);
+    if (rc) return rc;
+  }
+  // one partial per 256-row block, or per tile of at least 32 rows
+  CK(dalloc_t(c, &c->c_lpart, (size_t)(Bp / 32) * 3 * 8));
+  CK(dalloc_t(c, &c->a_lpart, (size_t)(Bp / 32) * 2 * 8));
   // streams (default priority)
   CK(hipStreamCreateWithFlags(&c->sc, hipStreamNonBlocking));
   CK(hipStreamCreateWithFlags(&c->sa, hipStreamNonBlocking));
@@ -1201,11 +1741,7 @@ int setup(spz_ctx* c) {
   host_init(c, img);
   CK(hipMemcpy(c->P, img.data(), ab, hipMemcpyHostToDevice));
   CK(hipMemcpy(c->T, img.data(), ab, hipMemcpyHostToDevice));
-  if (c->bf16) {
-    CK(launch_to_bf16(c->P, c->Pb, c->n_arena, c->sc));
-    CK(launch_to_bf16(c->T, c->Tb, c->n_arena, c->sc));
-    CK(refresh_wt(c, c->sc));
-  }
+  CK(refresh_images(c, c->sc));
   CK(hipStreamSynchronize(c->sc));
   CK(hipDeviceSynchronize());
   return SPZ_OK;
@@ -1534,6 +2070,13 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
     const int m = (int)std::min(chunk, n - r0);
     const int rows = (m + 255) / 256 * 256;
     hipError_t e = hipMemcpy(c->stage, obs + r0 * c->O, (size_t)m * c->O * 4, hipMemcpyHostToDevice);
+    if (c->rows_on) {
+      if (e == hipSuccess) e = row_act(c, c->stage, m, r0, stochastic != 0, counter, c->th, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      if (e == hipSuccess) e = hipMemcpy(act + r0 * c->A, c->th, (size_t)m * c->A * 4, hipMemcpyDeviceToHost);
+      if (e != hipSuccess) rc = set_err(c, SPZ_EHIP, std::string("spz_act: ") + hipGetErrorString(e));
+      continue;
+    }
     ObsArgs oa{c->stage, m, rows, c->O, c->Ka, c->xsp, c->Kc};
     if (e == hipSuccess) e = launch_obs_operand(c->bf16, oa, s);
     c->B = m;
@@ -1599,6 +2142,10 @@ int spz_act_noalloc(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic,
   uint8_t* base = static_cast<uint8_t*>(g_scratch_ptr[c->hp.device]);
   if (!base) return set_err(c, SPZ_EHIP, "spz_act_noalloc: scratch address not initialised");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if (c->rows_on) {   // needs no scratch
+    CK(row_act(c, obs, (int)n, 0, stochastic != 0, counter, act, s));
+    return SPZ_OK;
+  }
   const int rows = (int)((n + 255) / 256 * 256);
   size_t off[4];
   act_scratch_layout(c, rows, off);
@@ -1740,13 +2287,9 @@ int spz_load(spz_ctx* c, const char* path) {
     c->ptr = h.ring_ptr;
     c->size = h.ring_size;
   }
-  // The bf16 operand images are a pure function of the float32 parameters.
-  if (c->bf16) {
-    CK(launch_to_bf16(c->P, c->Pb, c->n_arena, c->sc));
-    CK(launch_to_bf16(c->T, c->Tb, c->n_arena, c->sc));
-    CK(refresh_wt(c, c->sc));
-    CK(hipStreamSynchronize(c->sc));
-  }
+  // The operand images are a pure function of the float32 parameters.
+  CK(refresh_images(c, c->sc));
+  CK(hipStreamSynchronize(c->sc));
   c->seed = h.seed;
   CK(hipMemcpy(c->d_step, &h.step, 8, hipMemcpyHostToDevice));
   c->h_step = h.step;
@@ -1757,7 +2300,7 @@ int spz_set_batch(spz_ctx* c, int32_t batch) {
   if (!c) return set_err(nullptr, SPZ_EINVAL, "spz_set_batch: NULL context");
   if (batch < 1 || batch > c->Bmax) return set_err(c, SPZ_EINVAL, "spz_set_batch: batch out of [1, created batch]");
   const int Bp = (batch + 255) / 256 * 256;
-  for (int q = 0; q < 2; ++q)
+  for (int q = 0; q < 2 && c->layers_ok; ++q)
     if (red_need(c, q, Bp) > c->red[q].cap)
       return set_err(c, SPZ_EINVAL, "spz_set_batch: reduction workspace too small for this batch");
   CK(hipSetDevice(c->hp.device));
@@ -1769,12 +2312,17 @@ int spz_set_batch(spz_ctx* c, int32_t batch) {
     const size_t e = es(c);
     const size_t pad = (size_t)(Bp - batch);
     for (void* x : {c->xsa, c->xs2, c->xsp})
-      CK(hipMemset(static_cast<uint8_t*>(x) + (size_t)batch * c->Kc * e, 0, pad * c->Kc * e));
+      if (x) CK(hipMemset(static_cast<uint8_t*>(x) + (size_t)batch * c->Kc * e, 0, pad * c->Kc * e));
     const int pa = c->net[0].L.back().out_p;
-    CK(hipMemset(static_cast<uint8_t*>(c->dzh) + (size_t)batch * pa * e, 0, pad * pa * e));
+    if (c->dzh) CK(hipMemset(static_cast<uint8_t*>(c->dzh) + (size_t)batch * pa * e, 0, pad * pa * e));
   }
   c->B = batch;
   c->Bp = Bp;
+  if (row_batch(c, batch) != c->rows_on) {   // a step keeps only its own path's images current
+    c->rows_on = !c->rows_on;
+    CK(refresh_images(c, c->sc));
+    CK(hipStreamSynchronize(c->sc));
+  }
   return SPZ_OK;
 }
 
@@ -1917,10 +2465,8 @@ int spz_write_params(spz_ctx* c, int32_t which, const float* in, int64_t n_float
     for (int r = 0; r < L.out_f; ++r) img[L.b - n.off + r] = in[o++];
   }
   CK(hipMemcpy(arena + n.off, img.data(), img.size() * 4, hipMemcpyHostToDevice));
-  if (c->bf16 && (arena == c->P || arena == c->T)) {
-    bf16_t* sh = arena == c->P ? c->Pb : c->Tb;
-    CK(launch_to_bf16(arena + n.off, sh + n.off, n.end - n.off, c->sc));
-    if (arena == c->P) CK(refresh_wt(c, c->sc));
+  if (arena == c->P || arena == c->T) {
+    CK(refresh_images(c, c->sc));
     CK(hipStreamSynchronize(c->sc));
   }
   return SPZ_OK;
@@ -1978,9 +2524,10 @@ int spz_debug_read(spz_ctx* c, int32_t what, void* out, int64_t bytes) {
     case SPZ_DBG_LOGPI: CK(hipMemcpy(f, c->logp, B * 4, hipMemcpyDeviceToHost)); break;
     case SPZ_DBG_BATCH: {
       // s from xsa, s' from xs2 (their first O columns), the actions from xsa's action
-      // columns where the step ran on two streams (the actor part had its own operand)
+      // columns where the step ran on two streams (the actor part had its own operand) or
+      // on the row-tile path (its operand stays in LDS)
       // and from the gather's copy otherwise, r and d from the arrays the TD target reads.
-      const bool two = c->hp.n_streams == 2 && c->hp.ordering != SPZ_ORDER_SEQUENTIAL;
+      const bool two = c->last_rows || (c->hp.n_streams == 2 && c->hp.ordering != SPZ_ORDER_SEQUENTIAL);
       const size_t e = es(c);
       std::vector<uint8_t> xa((size_t)B * c->Kc * e), x2((size_t)B * c->Kc * e), ab((size_t)B * c->A * e);
       std::vector<float> rr(B), dd(B);
@@ -2007,9 +2554,10 @@ int spz_debug_read(spz_ctx* c, int32_t what, void* out, int64_t bytes) {
       break;
     }
     case SPZ_DBG_DACTION: {
-      // da1 [Bp, Ap] holds the whole gradient under the SAC row split (and for TD3);
+      // da1 [Bp, Ap] holds the whole gradient under the SAC row split, on the row-tile path
+      // (and for TD3);
       // otherwise critic 2's part is in da2.
-      const bool two = !c->td3 && !c->row_split;
+      const bool two = !c->td3 && !c->row_split && !c->last_rows;
       std::vector<float> d1((size_t)B * c->Ap), d2(two ? (size_t)B * c->Ap : 0);
       CK(hipMemcpy(d1.data(), c->da1, d1.size() * 4, hipMemcpyDeviceToHost));
       if (two) CK(hipMemcpy(d2.data(), c->da2, d2.size() * 4, hipMemcpyDeviceToHost));

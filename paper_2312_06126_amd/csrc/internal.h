@@ -121,25 +121,33 @@ struct SacHeadArgs {
   float *th, *se, *lm;                 // backward cache [B, A] (null for the target side)
 };
 
-// Element (row b, action j) of the SAC head from its mean mu, log-std l and deviate eps
-// (normal_at of element b A + j at the step's counter word): stores the action (and the backward cache) and returns
-// the element's log-density term, in the overflow-free form of log(1 - tanh^2 u) =
-// 2 (ln 2 - u - softplus(-2u)). Shared by the head kernel and the head product's fused
-// epilogue, so both compute the same bits.
+// One element of the SAC head from its mean mu, log-std l and deviate eps: the action, its
+// cache for the backward pass and its log-density term, in the overflow-free form of
+// log(1 - tanh^2 u) = 2 (ln 2 - u - softplus(-2u)).
+struct SacHeadValue { float a, se, lm, term; };
+__device__ inline SacHeadValue sac_head_value(float mu, float l, float eps, float lmin, float lmax) {
+  const float lc = clamp_keep_nan(l, lmin, lmax);
+  const float sig = expf(lc);
+  const float u = mu + sig * eps;
+  return SacHeadValue{tanhf(u), sig * eps, (l >= lmin && l <= lmax) ? 1.0f : 0.0f,
+                      -0.5f * eps * eps - lc - HALF_LN_2PI_F - 2.0f * (LN2F - u - softplusf(-2.0f * u))};
+}
+
+// Element (row b, action j) of the head (eps: normal_at of element b A + j at the step's
+// counter word): stores the action (and the backward cache) and returns the log-density
+// term. Shared by the head kernel and the head product's fused epilogue, so both compute
+// the same bits.
 template <typename T>
 __device__ inline float sac_head_element(const SacHeadArgs& h, float mu, float l, int b, int j, float eps) {
   const uint64_t e = (uint64_t)b * h.A + j;
-  const float lc = clamp_keep_nan(l, h.lmin, h.lmax);
-  const float sig = expf(lc);
-  const float u = mu + sig * eps;
-  const float a = tanhf(u);
-  static_cast<T*>(h.x)[(int64_t)b * h.ldx + h.xoff + j] = from_f<T>(a);
+  const SacHeadValue v = sac_head_value(mu, l, eps, h.lmin, h.lmax);
+  static_cast<T*>(h.x)[(int64_t)b * h.ldx + h.xoff + j] = from_f<T>(v.a);
   if (h.th) {
-    h.th[e] = a;
-    h.se[e] = sig * eps;
-    h.lm[e] = (l >= h.lmin && l <= h.lmax) ? 1.0f : 0.0f;
+    h.th[e] = v.a;
+    h.se[e] = v.se;
+    h.lm[e] = v.lm;
   }
-  return -0.5f * eps * eps - lc - HALF_LN_2PI_F - 2.0f * (LN2F - u - softplusf(-2.0f * u));
+  return v.term;
 }
 
 // ----------------------------------------------------------------------------- GEMM

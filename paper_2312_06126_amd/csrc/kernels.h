@@ -124,7 +124,7 @@ struct ColsumArgs {
 };
 
 struct AdamArgs {
-  float *P, *M, *V, *T; const float* G; bf16_t *Pb, *Tb;
+  float *P, *M, *V, *T; float* G; bf16_t *Pb, *Tb;
   int64_t n, a0, a1, c0, c1, la;
   int do_actor, do_critic, do_alpha, polyak_critic, polyak_actor, td3, delay;
   float lr_a, lr_c, lr_al, b1, b2, eps, tau;
@@ -132,12 +132,100 @@ struct AdamArgs {
   int step_add;   // the step being completed is *step + step_add (1 before k_finish ran)
 };
 
+// Adam's bias corrections 1 - beta^t of the step being completed (beta1 / beta2 at t, then
+// at the actor's t: delayed steps for TD3), in double precision by the first four threads;
+// the caller synchronizes.
+__device__ inline void adam_corrections(const AdamArgs& a, float* bc) {
+  const int64_t t = *a.step + a.step_add;
+  if (threadIdx.x < 4) {
+    const double beta = (threadIdx.x & 1) ? (double)a.b2 : (double)a.b1;
+    bc[threadIdx.x] = (float)(1.0 - pow(beta, (double)(threadIdx.x < 2 ? t : (a.td3 ? t / a.delay : t))));
+  }
+}
+
+// One Adam step of a parameter (returned) and its moments.
+__device__ inline float adam_element(const AdamArgs& a, float p, float& m, float& v, float g, float lr, float bc1,
+                                     float bc2) {
+  m = a.b1 * m + (1.0f - a.b1) * g;
+  v = a.b2 * v + (1.0f - a.b2) * g * g;
+  return p - lr * (m / bc1) / (sqrtf(v / bc2) + a.eps);
+}
+
 struct FinishArgs {
   const double *cpart, *apart; int nc, na, B;
   int sac, actor_step, learn_alpha; float target_entropy;
   const float* log_alpha; float* grad_alpha;
   float* rec; int64_t rec_cap; int64_t* step;
 };
+
+// Minimum that keeps a NaN operand (fminf would drop it), like clamp_keep_nan.
+__device__ inline float min_keep_nan(float a, float b) { return (a < b || a != a) ? a : b; }
+
+// Sum of a double over a block of NT threads (sh: NT doubles of LDS), a fixed tree.
+template <int NT>
+__device__ inline double block_sum(double v, double* sh) {
+  const int t = threadIdx.x;
+  sh[t] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = NT / 2; s > 0; s >>= 1) {
+    if (t < s) sh[t] += sh[t + s];
+    __syncthreads();
+  }
+  const double r = sh[0];
+  __syncthreads();
+  return r;
+}
+
+// One block of 256 threads (sh: 256 doubles of LDS): reduce the step's loss partials in index order, write the loss
+// record, the temperature gradient, and advance the device step counter.
+__device__ inline void finish_step(const FinishArgs& f, double* sh) {
+  double e1 = 0.0, e2 = 0.0, q1 = 0.0, l0 = 0.0, l1 = 0.0;
+  for (int i = threadIdx.x; i < f.nc; i += 256) {
+    e1 += f.cpart[i * 3 + 0];
+    e2 += f.cpart[i * 3 + 1];
+    q1 += f.cpart[i * 3 + 2];
+  }
+  if (f.actor_step)
+    for (int i = threadIdx.x; i < f.na; i += 256) {
+      l0 += f.apart[i * 2 + 0];
+      l1 += f.apart[i * 2 + 1];
+    }
+  e1 = block_sum<256>(e1, sh);
+  e2 = block_sum<256>(e2, sh);
+  q1 = block_sum<256>(q1, sh);
+  l0 = block_sum<256>(l0, sh);
+  l1 = block_sum<256>(l1, sh);
+  if (threadIdx.x != 0) return;
+  const int64_t t = *f.step + 1;
+  const double invB = 1.0 / (double)f.B;
+  float rec[SPZ_REC_WIDTH];
+  rec[SPZ_REC_LQ] = (float)((e1 + e2) * invB);
+  rec[SPZ_REC_Q1] = (float)(q1 * invB);
+  rec[SPZ_REC_LPI] = 0.0f;
+  rec[SPZ_REC_LALPHA] = 0.0f;
+  rec[SPZ_REC_ALPHA] = 0.0f;
+  rec[SPZ_REC_LOGPI] = 0.0f;
+  if (f.sac) {
+    const float log_alpha = *f.log_alpha;
+    const double mean_lp = l1 * invB;
+    rec[SPZ_REC_LPI] = (float)(l0 * invB);
+    rec[SPZ_REC_LOGPI] = (float)mean_lp;
+    rec[SPZ_REC_ALPHA] = expf(log_alpha);
+    const double mh = mean_lp + (double)f.target_entropy;
+    rec[SPZ_REC_LALPHA] = (float)(-(double)log_alpha * mh);
+    if (f.grad_alpha) *f.grad_alpha = f.learn_alpha ? (float)(-mh) : 0.0f;
+  } else if (f.actor_step) {
+    rec[SPZ_REC_LPI] = (float)(-l0 * invB);
+  }
+  bool bad = false;
+  for (int i = 0; i < 6; ++i) bad = bad || !isfinite(rec[i]);
+  rec[SPZ_REC_NONFINITE] = bad ? 1.0f : 0.0f;
+  rec[SPZ_REC_ACTOR] = f.actor_step ? 1.0f : 0.0f;
+  float* dst = f.rec + ((t - 1) % f.rec_cap) * SPZ_REC_WIDTH;
+  for (int i = 0; i < SPZ_REC_WIDTH; ++i) dst[i] = rec[i];
+  *f.step = t;
+}
 
 hipError_t launch_gather(bool bf16, const GatherArgs& g, hipStream_t s);
 hipError_t launch_pack(bool bf16, const PackArgs& p, hipStream_t s);

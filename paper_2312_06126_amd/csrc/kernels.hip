@@ -11,24 +11,6 @@
 namespace spz {
 namespace {
 
-// Minimum that keeps a NaN operand (fminf would drop it), like clamp_keep_nan.
-__device__ inline float min_keep_nan(float a, float b) { return (a < b || a != a) ? a : b; }
-
-template <int NT>
-__device__ inline double block_sum(double v, double* sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] += sh[t + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
 // Sum of an int over a 256-thread block (4 waves of 64 lanes).
 __device__ inline int block_sum_i32(int v, int* sh) {
 #pragma unroll
@@ -672,15 +654,8 @@ __global__ void __launch_bounds__(256) k_reduce_jobs(ReduceJobs J) {
 // range and log(alpha); then Polyak tbar <- (1 - tau) tbar + tau theta on the
 // target ranges; refreshes the bfloat16 shadows of what it wrote.
 __global__ void __launch_bounds__(256) k_adam_polyak(AdamArgs a) {
-  // Bias corrections 1 - beta^t of the step (actor: delayed-step count for TD3),
-  // computed once per block in double precision.
   __shared__ float bc[4];   // beta1 / beta2 corrections at t, then at the actor's t
-  const int64_t t = *a.step + a.step_add;
-  const int64_t ta = a.td3 ? t / a.delay : t;
-  if (threadIdx.x < 4) {
-    const double beta = (threadIdx.x & 1) ? (double)a.b2 : (double)a.b1;
-    bc[threadIdx.x] = (float)(1.0 - pow(beta, (double)(threadIdx.x < 2 ? t : ta)));
-  }
+  adam_corrections(a, bc);
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
@@ -701,13 +676,10 @@ __global__ void __launch_bounds__(256) k_adam_polyak(AdamArgs a) {
   } else {
     return;
   }
-  const float bc1 = bc[sel], bc2 = bc[sel + 1];
-  const float g = a.G[i];
-  const float m = a.b1 * a.M[i] + (1.0f - a.b1) * g;
-  const float v = a.b2 * a.V[i] + (1.0f - a.b2) * g * g;
+  float m = a.M[i], v = a.V[i];
+  const float p = adam_element(a, a.P[i], m, v, a.G[i], lr, bc[sel], bc[sel + 1]);
   a.M[i] = m;
   a.V[i] = v;
-  const float p = a.P[i] - lr * (m / bc1) / (sqrtf(v / bc2) + a.eps);
   a.P[i] = p;
   if (a.Pb) a.Pb[i] = f2bf(p);
   const bool pol = (in_critic && a.polyak_critic) || (in_actor && a.polyak_actor);
@@ -718,55 +690,9 @@ __global__ void __launch_bounds__(256) k_adam_polyak(AdamArgs a) {
   }
 }
 
-// One block: reduce the step's loss partials in index order, write the loss
-// record, the temperature gradient, and advance the device step counter.
 __global__ void __launch_bounds__(256) k_finish(FinishArgs f) {
   __shared__ double sh[256];
-  double e1 = 0.0, e2 = 0.0, q1 = 0.0, l0 = 0.0, l1 = 0.0;
-  for (int i = threadIdx.x; i < f.nc; i += 256) {
-    e1 += f.cpart[i * 3 + 0];
-    e2 += f.cpart[i * 3 + 1];
-    q1 += f.cpart[i * 3 + 2];
-  }
-  if (f.actor_step)
-    for (int i = threadIdx.x; i < f.na; i += 256) {
-      l0 += f.apart[i * 2 + 0];
-      l1 += f.apart[i * 2 + 1];
-    }
-  e1 = block_sum<256>(e1, sh);
-  e2 = block_sum<256>(e2, sh);
-  q1 = block_sum<256>(q1, sh);
-  l0 = block_sum<256>(l0, sh);
-  l1 = block_sum<256>(l1, sh);
-  if (threadIdx.x != 0) return;
-  const int64_t t = *f.step + 1;
-  const double invB = 1.0 / (double)f.B;
-  float rec[SPZ_REC_WIDTH];
-  rec[SPZ_REC_LQ] = (float)((e1 + e2) * invB);
-  rec[SPZ_REC_Q1] = (float)(q1 * invB);
-  rec[SPZ_REC_LPI] = 0.0f;
-  rec[SPZ_REC_LALPHA] = 0.0f;
-  rec[SPZ_REC_ALPHA] = 0.0f;
-  rec[SPZ_REC_LOGPI] = 0.0f;
-  if (f.sac) {
-    const float log_alpha = *f.log_alpha;
-    const double mean_lp = l1 * invB;
-    rec[SPZ_REC_LPI] = (float)(l0 * invB);
-    rec[SPZ_REC_LOGPI] = (float)mean_lp;
-    rec[SPZ_REC_ALPHA] = expf(log_alpha);
-    const double mh = mean_lp + (double)f.target_entropy;
-    rec[SPZ_REC_LALPHA] = (float)(-(double)log_alpha * mh);
-    if (f.grad_alpha) *f.grad_alpha = f.learn_alpha ? (float)(-mh) : 0.0f;
-  } else if (f.actor_step) {
-    rec[SPZ_REC_LPI] = (float)(-l0 * invB);
-  }
-  bool bad = false;
-  for (int i = 0; i < 6; ++i) bad = bad || !isfinite(rec[i]);
-  rec[SPZ_REC_NONFINITE] = bad ? 1.0f : 0.0f;
-  rec[SPZ_REC_ACTOR] = f.actor_step ? 1.0f : 0.0f;
-  float* dst = f.rec + ((t - 1) % f.rec_cap) * SPZ_REC_WIDTH;
-  for (int i = 0; i < SPZ_REC_WIDTH; ++i) dst[i] = rec[i];
-  *f.step = t;
+  finish_step(f, sh);
 }
 
 __global__ void __launch_bounds__(256) k_to_bf16(const float* __restrict__ src, bf16_t* __restrict__ dst, int64_t n) {

@@ -1,0 +1,70 @@
+"""GPU tests of the row-tile path at the edges of what it takes: one hidden layer, the widest
+layers it accepts (one critic at a time), heads of 1 and 32 actions, batches below, at and
+past its tiles, and the batch at which networks with the row split change paths."""
+import numpy as np
+import pytest
+
+import synth
+from synth.workloads import Workload
+
+from .helpers import log, make_gpu
+from .test_gpu_parity import BF16_LOSS_TOL, FP32_TOL, FUSED_BF16, RAGGED, RAGGED_TD3, teacher_forced
+
+pytestmark = pytest.mark.gpu
+
+WIDE = Workload("wide_rows", "sac", 376, 32, (512, 480), 200, 4000, "fp32", 10, target_entropy=-32.0)
+CASES = [
+    RAGGED.replace(name="one_layer", hidden=(32,), act_dim=1, batch=1),
+    RAGGED.replace(name="one_wide_layer_td3", algo="td3", hidden=(416,), batch=33, learn_alpha=False, alpha_init=0.0),
+    WIDE,                                                        # one critic at a time
+    WIDE.replace(name="wide_rows_bf16", prec="bf16", hidden=(480, 512, 96)),
+    RAGGED_TD3.replace(name="deep_td3", hidden=(40, 300, 64, 33), obs_dim=65, act_dim=33, batch=97),
+    FUSED_BF16.replace(name="tiles64", batch=16385, hidden=(128, 128)),   # 64-row tiles, a ragged last one
+]
+
+
+@pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
+def test_row_path_teacher_forced(w):
+    """Every gradient tensor, Adam's moments and the losses of one step from the oracle's state
+    (bounds as for the other teacher-forced tests: 1e-4 in float32, 1e-3 in bfloat16)."""
+    log("row path %s" % w.name)
+    g = make_gpu(w)
+    g.buffer_push(*synth.workload_rows(w, 0, 1000, 0))
+    g.profile_enable(True, 100)
+    g.update(1)
+    names = {s["name"] for s in g.profile_read()}
+    g.close()
+    assert names == {"gather", "row_step", "row_wgrad", "row_adam"}, names
+    bf16 = w.prec == "bf16"
+    teacher_forced(w, 4000, steps_before=1, n_steps=2, tol_grad=1e-3 if bf16 else FP32_TOL,
+                   tol_loss=BF16_LOSS_TOL if bf16 else FP32_TOL)
+
+
+@pytest.mark.parametrize("b", [500, 1024, 1500])
+def test_set_batch_across_the_path_change_bit_exact(b):
+    """A context created for 2048 rows, having run steps there, computes at batch b what a
+    context created with b does from the same state, whichever path either batch takes."""
+    w = FUSED_BF16
+    out = []
+    state = None
+    for created in (2048, b):
+        g = make_gpu(w.replace(batch=created))
+        g.buffer_push(*synth.workload_rows(w, 0, 5000, 0))
+        keys = ["actor", "critic1", "critic2", "tcritic1", "tcritic2", "log_alpha"]
+        keys += [m + k for m in ("m_", "v_") for k in ("actor", "critic1", "critic2", "log_alpha")]
+        if state is None:
+            g.update(2)
+            state = {k: g.read_params(k) for k in keys}
+            g.set_batch(b)
+        else:
+            for k in keys:
+                g.write_params(k, state[k])
+            g.set_step(2)
+        g.update(2)
+        obs = synth.workload_rows(w, 0, 40, 3)[0]
+        out.append({k: g.read_params(k) for k in keys})
+        out[-1].update(rec=g.read_losses(3, 2), idx=g.debug_indices(), act=g.act(obs, True, 5),
+                       da=g.debug_rows("daction"), batch=np.concatenate([np.ravel(x) for x in g.debug_batch()]))
+        g.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
