@@ -173,15 +173,14 @@ struct spz_ctx {
   // Row-tile path (rows.h): available when the networks fit it; whether the layer-by-layer
   // path's buffers exist; which of the two the current batch takes; what the last step took.
   struct RowPlan {   // one per tile height (index tm - 1)
+    int nets = 2;          // nets per operation where both critics run
     RowOp* ops = nullptr;
     int n_crit = 0, n_act = 0, n_sampler = 0;   // consecutive in ops
-    int max_blocks = 0;
     RowArgs lay{};     // LDS layout
     size_t lds = 0;
   };
   RowPlan rplan[2];
   bool rows_ok = false, layers_ok = false, rows_on = false, last_rows = false;
-  int rows_nets = 2;             // nets per operation where both critics run
   void *xpk = nullptr, *dzh_pk = nullptr;
   std::vector<void*> hpk[3], dzpk[3];      // per net and hidden layer: packed activations and gradients
   std::vector<float*> bpart[3];            // per net and layer: bias-gradient partials
@@ -938,26 +937,29 @@ int row_vec(const spz_ctx* c) { return c->bf16 ? 8 : 4; }
 int row_ks(const spz_ctx* c) { return c->bf16 ? 16 : 8; }
 size_t align16z(size_t x) { return (x + 15) / 16 * 16; }
 
-// LDS layout of a tile of 32 tm rows with `nets` critics side by side; returns its bytes.
-size_t row_layout(const spz_ctx* c, int tm, int nets, RowArgs& g) {
+// LDS layout of a tile of 32 tm rows with `nets` critics side by side; returns its bytes. The scratch area takes the partial blocks of products split over waves.
+size_t row_layout(const spz_ctx* c, int tm, int nets, size_t scratch, RowArgs& g) {
   const int bm = 32 * tm, pa = c->net[0].L.back().out_p, nh = (int)c->hidden.size();
   const size_t e = es(c);
   g.tm = tm;
   g.ldx = c->Kc + row_vec(c);
   g.ldh = std::max(c->hmax, pa) + row_vec(c);
   g.hnet = bm * g.ldh;
-  g.zp = std::max(pa, c->Ap) + 1;
+  g.zp = pa + 4;   // 16-byte rows
+  g.dp = c->Ap + 4;
   size_t off = 0;
-  g.oX = 0;
+  g.oX = (int)off;
   off += align16z((size_t)bm * g.ldx * e);
   g.oH = (int)off;
   off += align16z((size_t)nets * g.hnet * e);
   g.oZ = (int)off;   // actor output [bm, pa], or the two action gradients [bm, Ap]
-  off += align16z((size_t)std::max(bm * g.zp, c->td3 ? 0 : 2 * bm * g.zp) * 4);
+  off += align16z((size_t)bm * std::max(g.zp, (c->td3 ? 1 : 2) * g.dp) * 4);
   g.oV = (int)off;
   off += (size_t)6 * bm * 4;
   g.oM = (int)off;   // mask bits: actor layers, then each layer of both critics
   for (int l = 0; l < nh; ++l) off += (size_t)3 * bm * pad32(c->hidden[l]) / 8;
+  g.oS = (int)off;
+  off += scratch;
   g.A = c->A; g.Ka = c->Ka; g.Ap = c->Ap; g.Kc = c->Kc; g.pa = pa; g.O = c->O; g.sac = c->td3 ? 0 : 1;
   return off;
 }
@@ -970,26 +972,37 @@ int row_blocks(const spz_ctx* c, int nets) {
   return std::max(m, (c->Ap / 32 + wpn - 1) / wpn);
 }
 
-// Whether the networks fit the row-tile path (sets rows_nets: both critics side by side, or
-// one after the other where LDS or the blocks per wave do not allow it). Policy heads of up to
-// 64 outputs, as for the head fused into the output product.
-constexpr int ROW_MAX_WIDTH = 512;
-bool row_fits(spz_ctx* c) {
-  if (c->net[0].L.back().out_p > 64 || c->hmax > ROW_MAX_WIDTH) return false;
-  for (int nets = 2; nets >= 1; --nets) {
+// Nets per operation of tiles of 32 tm rows, 0 if the networks do not fit: both critics side by
+// side or one after the other, whichever lets more workgroups share a CU's LDS (2 x 256 fp32,
+// 8192 rows: 219 us for the step's row operations side by side, one workgroup per CU, and 189 us
+// one after the other, two per CU; side by side is faster where both allow as many: 2 x 256
+// bf16, 16384 rows, 137 and 150 us).
+int row_nets(const spz_ctx* c, int tm) {
+  int best = 0, nets = 0;
+  for (int n = 2; n >= 1; --n) {
     RowArgs g{};
-    if (row_blocks(c, nets) <= ROW_MAX_BLOCKS && row_layout(c, 1, nets, g) <= ROW_LDS_MAX) {
-      c->rows_nets = nets;
-      return true;
-    }
+    const size_t lds = row_layout(c, tm, n, 0, g);
+    if (row_blocks(c, n) > ROW_MAX_BLOCKS || lds > ROW_LDS_MAX) continue;
+    const int per_cu = tm == 1 && lds <= ROW_LDS_MAX / 2 ? 2 : 1;
+    if (per_cu <= best) continue;
+    best = per_cu;
+    nets = n;
   }
-  return false;
+  return nets;
+}
+
+// Whether the networks fit the row-tile path. Policy heads of up to 64 outputs, as for the
+// head fused into the output product.
+constexpr int ROW_MAX_WIDTH = 512;
+bool row_fits(const spz_ctx* c) {
+  return c->net[0].L.back().out_p <= 64 && c->hmax <= ROW_MAX_WIDTH && row_nets(c, 1) > 0;
 }
 
 // SAC networks whose layers all have mask bits (bf16, 128-multiple widths) keep the
 // layer-by-layer path, with its row split and one timing record per product, below this
 // batch: observers of small runs (spz_profile_*) see there what they always saw. The row-tile
-// path is the faster one on both sides of the line (256-128 bf16 at 500 rows: about a third).
+// path is the faster one on both sides of the line (256-128 bf16, 45 inputs, two streams:
+// layer by layer 198 us a step at 512 rows and 213 us at 1536, 62 us there in row tiles).
 constexpr int ROW_MIN_SPLIT_BATCH = 1024;
 bool row_batch(const spz_ctx* c, int batch) {
   if (!c->rows_ok) return false;
@@ -999,15 +1012,21 @@ bool row_batch(const spz_ctx* c, int batch) {
   return batch >= ROW_MIN_SPLIT_BATCH;
 }
 
-// Rows per tile (in units of 32) for a batch.
+// Tile height (in units of 32 rows) for a batch. A bf16 product is bound by the weights' way
+// through the vector L1 (64 bytes a clock: 256 KB of the twin critics' 256 x 256 layer take
+// 4096 clocks, its matrix instructions for 32 rows 2048), so 64 rows a tile halve that where
+// the tiles of a step's two halves still give each CU one (2 x 256, 16384 rows: 134.6 us in
+// 32-row tiles, 132.7 in 64-row ones; 4096 rows: 25.3 and 28.7 us).
 int row_tm(const spz_ctx* c, int batch) {
-  return c->bf16 && c->rplan[1].ops && (batch + 63) / 64 >= 256 ? 2 : 1;
+  return c->rplan[1].ops && batch >= 64 * 128 ? 2 : 1;
 }
+int row_tile_count(int rows, int tm) { return (rows + 32 * tm - 1) / (32 * tm); }
 
 // The operations of the critic part, the actor part and the sampler-action call.
 struct RowBuilder {
   spz_ctx* c;
   int tm, nets;
+  size_t scratch;        // bytes of the scratch area products may be split into
   std::vector<RowOp> v;
   int nh, nl;
   int mask_at(int ni, int l) const {   // u16 index of layer l's mask bits
@@ -1025,12 +1044,27 @@ struct RowBuilder {
     o.kind = kind;
     o.nets = 1;
     o.mask = -1;
+    o.split = 1;
     return o;
+  }
+  // A product: with fewer blocks than waves, each block's steps are split over idle waves
+  // (the partial blocks meet in the scratch area). Not in a step's float32 forward products,
+  // whose sums stay in the order of the layer-by-layer products (the actor's output at 2 x
+  // 256: 15 thousand clocks a tile of 360 thousand, 5 when split).
+  bool step = true;
+  void product(RowOp o) {
+    const int wpn = ROW_WAVES / o.nets;
+    const bool split = c->bf16 || !step || (o.kind != ROW_HIDDEN && o.kind != ROW_Z);
+    while (split && 2 * o.split * o.nblk <= wpn && o.steps >= 4 * o.split &&
+           (size_t)(2 * o.split - 1) * o.nblk * o.nets * tm * 4096 <= scratch)
+      o.split *= 2;
+    v.push_back(o);
   }
   const void* pk(const void* base, int64_t off) const { return elem(c, base, off); }
   // Layers of nets ni .. ni + n - 1 (target: target parameters) from X; hidden layers keep
   // mask bits and packed images when asked.
-  void forward(int ni, int n, bool target, bool masks, bool packs) {
+  // Critics end in their output layer and `then`.
+  void forward(int ni, int n, bool target, bool masks, bool packs, int then = ROW_DOT_ONLY) {
     const int ks = row_ks(c);
     const int last = ni == 0 ? nl : nl - 1;
     for (int l = 0; l < last; ++l) {
@@ -1042,36 +1076,48 @@ struct RowBuilder {
         const Lay& Lk = c->net[ni + k].L[l];
         o.w[k] = pk(target ? c->TF : c->PF, Lk.w);
         o.bias[k] = wf(c, target, Lk.b);
-        if (l < nl - 1 && packs) o.pack[k] = c->hpk[ni + k][l];
+        // (side by side, the critics' last hidden layer is packed with its weighted sums,
+        // once dq is known)
+        if (l < nl - 1 && packs && !(n == 2 && l == nl - 2)) o.pack[k] = c->hpk[ni + k][l];
       }
-      v.push_back(o);
+      product(o);
     }
     if (ni == 0) return;
     const Lay& L = c->net[ni].L[nl - 1];
     RowOp o = op(ROW_DOT);
-    o.net0 = ni; o.nets = n; o.nblk = L.in_p / 32;
+    o.net0 = ni; o.nets = n; o.nblk = L.in_p / 32; o.flags = then;
+    if (then == ROW_DOT_CLOSS)
+      for (int k = 0; k < 2; ++k) o.part[k] = c->bpart[1 + k][nl - 1];
     for (int k = 0; k < n; ++k) {
-      o.w[k] = wf(c, target, c->net[ni + k].L[nl - 1].w);
+      o.w[k] = pk(target ? c->TF : c->PF, c->net[ni + k].L[nl - 1].w);
       o.bias[k] = wf(c, target, c->net[ni + k].L[nl - 1].b);
     }
     v.push_back(o);
   }
-  void critics(bool target, bool masks, bool packs, int count) {
-    for (int ni = 1; ni <= count; ni += nets) forward(ni, std::min(nets, count), target, masks, packs);
+  void critics(bool target, bool masks, bool packs, int count, int then) {
+    for (int ni = 1; ni <= count; ni += nets) {
+      const int n = std::min(nets, count);
+      forward(ni, n, target, masks, packs, ni + n > count ? then : ROW_DOT_ONLY);
+    }
+  }
+  void grad_outputs(RowOp& o, int ni, int n, int l) {
+    for (int k = 0; k < n; ++k) {
+      o.pack[k] = c->dzpk[ni + k][l];
+      o.part[k] = c->bpart[ni + k][l];
+    }
   }
   // From dq to the gradient of the first hidden layer (grads: the critics' own gradients).
   void critic_back(int ni, int n, bool grads) {
-    RowOp o = op(ROW_DZ);
     const Lay& H = c->net[ni].L[nl - 1];
-    o.net0 = ni; o.nets = n; o.nblk = H.in_p / 32; o.mask = mask_at(ni, nl - 2);
+    RowOp o = op(ROW_DZ);
+    o.net0 = ni; o.nets = n; o.nblk = H.in_p / 32; o.mask = mask_at(ni, nl - 2); o.flags = n == 1;
     for (int k = 0; k < n; ++k) {
-      o.w[k] = wf(c, false, c->net[ni + k].L[nl - 1].w);
+      o.w[k] = pk(c->PF, c->net[ni + k].L[nl - 1].w);
       if (!grads) continue;
-      o.pack[k] = c->dzpk[ni + k][nl - 2];
-      o.part[k] = c->bpart[ni + k][nl - 2];
-      o.wpart[k] = c->wpart_out[ni + k];
       o.hpack[k] = c->hpk[ni + k][nl - 2];
+      o.wpart[k] = c->wpart_out[ni + k];
     }
+    if (grads) grad_outputs(o, ni, n, nl - 2);
     v.push_back(o);
     for (int l = nl - 2; l >= 1; --l) dgrad(ni, n, l, grads);
   }
@@ -1080,18 +1126,18 @@ struct RowBuilder {
     RowOp o = op(ROW_DGRAD);
     o.net0 = ni; o.nets = n; o.nblk = L.in_p / 32; o.steps = L.out_p / row_ks(c); o.from_h = 1;
     o.mask = mask_at(ni, l - 1);
-    for (int k = 0; k < n; ++k) {
-      o.w[k] = pk(c->PT, c->net[ni + k].L[l].w);
-      if (!grads) continue;
-      o.pack[k] = c->dzpk[ni + k][l - 1];
-      o.part[k] = c->bpart[ni + k][l - 1];
-    }
-    v.push_back(o);
+    for (int k = 0; k < n; ++k) o.w[k] = pk(c->PT, c->net[ni + k].L[l].w);
+    if (grads) grad_outputs(o, ni, n, l - 1);
+    product(o);
   }
   void load(bool xsa, bool pack) {
     RowOp o = op(ROW_LOAD);
     o.flags = xsa;
-    if (pack) o.pack[0] = c->xpk;
+    v.push_back(o);
+    if (!pack) return;
+    o = op(ROW_PACK);
+    o.nblk = c->Kc / 32;
+    o.pack[0] = c->xpk;
     v.push_back(o);
   }
   void head(bool policy) {
@@ -1103,13 +1149,9 @@ struct RowBuilder {
     load(false, false);
     forward(0, 1, c->td3, false, false);
     head(false);
-    critics(true, false, false, 2);
-    v.push_back(op(ROW_TARGET));
+    critics(true, false, false, 2, ROW_DOT_TARGET);
     load(true, true);
-    critics(false, true, true, 2);
-    RowOp o = op(ROW_CLOSS);
-    for (int k = 0; k < 2; ++k) o.part[k] = c->bpart[1 + k][nl - 1];
-    v.push_back(o);
+    critics(false, true, true, 2, ROW_DOT_CLOSS);
     for (int ni = 1; ni <= 2; ni += nets) critic_back(ni, nets, true);
   }
   void actor_part() {
@@ -1117,8 +1159,7 @@ struct RowBuilder {
     load(true, false);
     forward(0, 1, false, true, true);
     head(true);
-    critics(false, true, false, n);
-    v.push_back(op(ROW_ALOSS));
+    critics(false, true, false, n, ROW_DOT_ALOSS);
     for (int ni = 1; ni <= n; ni += nets) {
       const int m = std::min(nets, n);
       critic_back(ni, m, false);
@@ -1126,16 +1167,18 @@ struct RowBuilder {
       const Lay& L = c->net[ni].L[0];
       o.net0 = ni; o.nets = m; o.nblk = c->Ap / 32; o.steps = L.out_p / row_ks(c); o.from_h = 1;
       for (int k = 0; k < m; ++k) o.w[k] = pk(c->PT, c->net[ni + k].L[0].w);
-      v.push_back(o);
+      product(o);
     }
-    RowOp o = op(ROW_HEAD_BWD);
-    o.nblk = c->net[0].L.back().out_p / 32;
+    v.push_back(op(ROW_HEAD_BWD));
+    RowOp o = op(ROW_PACK);
+    o.nblk = c->net[0].L.back().out_p / 32; o.from_h = 1;
     o.pack[0] = c->dzh_pk;
     o.part[0] = c->bpart[0][nl - 1];
     v.push_back(o);
     for (int l = nl - 1; l >= 1; --l) dgrad(0, 1, l, true);
   }
   void sampler() {
+    step = false;
     v.push_back(op(ROW_OBS));
     forward(0, 1, false, false, false);
     v.push_back(op(ROW_ACT));
@@ -1186,7 +1229,7 @@ int setup_rows(spz_ctx* c) {
   const int64_t Bp = c->Bp;
   const int nh = (int)c->hidden.size(), nl = nh + 1;
   const int pa = c->net[0].L.back().out_p;
-  const size_t nt = (size_t)Bp / 32;   // the most tiles
+  const size_t nt = (size_t)Bp / ROW_MIN_TILE;   // the most tiles
   CK(dalloc(c, &c->PF, (size_t)c->n_arena * e));
   CK(dalloc(c, &c->PT, (size_t)c->n_arena * e));
   CK(dalloc(c, &c->TF, (size_t)c->n_arena * e));
@@ -1201,7 +1244,8 @@ int setup_rows(spz_ctx* c) {
       CK(dalloc(c, &c->hpk[ni][l], b));
       CK(dalloc(c, &c->dzpk[ni][l], b));
     }
-    for (int l = 0; l < nl; ++l) CK(dalloc_t(c, &c->bpart[ni][l], nt * c->net[ni].L[l].out_p * 4));
+    for (int l = 0; l < nl; ++l)   // (a critic's output layer: per wave)
+      CK(dalloc_t(c, &c->bpart[ni][l], nt * (ni && l == nl - 1 ? ROW_WAVES : c->net[ni].L[l].out_p) * 4));
     if (ni) CK(dalloc_t(c, &c->wpart_out[ni], nt * c->net[ni].L[nl - 1].in_p * 4));
   }
   // Weight-gradient slices: a step's launches use the workspace one after the other; slice
@@ -1241,18 +1285,19 @@ int setup_rows(spz_ctx* c) {
           blk.push_back(b);
         }
     }
-    auto vec = [&](int ni, int64_t off, const float* p, int n) {
+    auto vec = [&](int ni, int64_t off, const float* p, int n, bool image) {
       for (int i = 0; i < n; i += 16) {
         RowPBlk b{};
         b.kind = 1; b.net = ni; b.off = off + i; b.ld = n; b.part = p + i;
+        b.fwd = image ? b.off : -1;
         blk.push_back(b);
       }
     };
     for (int ni = part ? 0 : 1; ni <= (part ? 0 : 2); ++ni) {
-      for (int l = 0; l < (part ? nl : nl - 1); ++l) vec(ni, c->net[ni].L[l].b, c->bpart[ni][l], c->net[ni].L[l].out_p);
+      for (int l = 0; l < (part ? nl : nl - 1); ++l) vec(ni, c->net[ni].L[l].b, c->bpart[ni][l], c->net[ni].L[l].out_p, false);
       if (!part) {
         const Lay& H = c->net[ni].L[nl - 1];
-        vec(ni, H.w, c->wpart_out[ni], H.in_p);
+        vec(ni, H.w, c->wpart_out[ni], H.in_p, true);
         RowPBlk b{};
         b.kind = 2; b.net = ni; b.off = H.b; b.part = c->bpart[ni][nl - 1];
         blk.push_back(b);
@@ -1269,19 +1314,23 @@ int setup_rows(spz_ctx* c) {
   }
   CK(dalloc_t(c, &c->pblk, blk.size() * sizeof(RowPBlk)));
   CK(hipMemcpy(c->pblk, blk.data(), blk.size() * sizeof(RowPBlk), hipMemcpyHostToDevice));
-  // operation lists
+  // Operation lists. The scratch area gets what LDS has left without lowering the workgroups
+  // per CU, up to one partial block for each of the other waves.
   for (int tm = 1; tm <= (c->bf16 ? 2 : 1); ++tm) {
     spz_ctx::RowPlan& P = c->rplan[tm - 1];
-    P.lds = row_layout(c, tm, c->rows_nets, P.lay);
-    if (P.lds > ROW_LDS_MAX) continue;
-    RowBuilder b{c, tm, c->rows_nets, {}, nh, nl};
+    P.nets = row_nets(c, tm);
+    if (!P.nets) continue;
+    const size_t base = row_layout(c, tm, P.nets, 0, P.lay);
+    const size_t cap = tm == 1 && base <= ROW_LDS_MAX / 2 ? ROW_LDS_MAX / 2 : ROW_LDS_MAX;
+    const size_t scratch = std::min<size_t>(cap - base, (size_t)(ROW_WAVES - 1) * tm * 4096) / 4096 * 4096;
+    P.lds = row_layout(c, tm, P.nets, scratch, P.lay);
+    RowBuilder b{c, tm, P.nets, scratch, {}, nh, nl};
     b.critic_part();
     P.n_crit = (int)b.v.size();
     b.actor_part();
     P.n_act = (int)b.v.size() - P.n_crit;
     b.sampler();
     P.n_sampler = (int)b.v.size() - P.n_crit - P.n_act;
-    P.max_blocks = row_blocks(c, c->rows_nets);
     CK(dalloc_t(c, &P.ops, b.v.size() * sizeof(RowOp)));
     CK(hipMemcpy(P.ops, b.v.data(), b.v.size() * sizeof(RowOp), hipMemcpyHostToDevice));
   }
@@ -1295,7 +1344,7 @@ hipError_t row_step(spz_ctx* c, bool crit, bool act, hipStream_t s) {
   const spz_ctx::RowPlan& P = c->rplan[tm - 1];
   RowArgs g = P.lay;
   g.ops = P.ops;
-  g.tiles = (c->B + 32 * tm - 1) / (32 * tm);
+  g.tiles = row_tile_count(c->B, tm);
   g.parts = (crit ? 1 : 0) + (act ? 1 : 0);
   int i = 0;
   if (crit) { g.op0[i] = 0; g.nops[i++] = P.n_crit; }
@@ -1315,14 +1364,14 @@ hipError_t row_step(spz_ctx* c, bool crit, bool act, hipStream_t s) {
   if (crit) macs += fw(0) + 4 * fw(1) + 2 * bw(1);
   if (act) macs += fw(0) + bw(0) + (c->td3 ? 1 : 2) * (fw(1) + bw(1));
   return timed(c, "row_step", g.tiles * 32 * tm, g.parts, c->hmax, 2.0 * c->B * macs, 0.0, s,
-               [&] { return launch_rows(c->bf16, g, P.max_blocks, P.lds, s); });
+               [&] { return launch_rows(c->bf16, g, P.lds, s); });
 }
 
 // Weight gradients of the critics and / or the actor, with the step's finish when asked;
 // then their reduction and Adam (+ Polyak, a) and the packed images.
 hipError_t row_update(spz_ctx* c, bool crit, bool act, const FinishArgs* fin, const AdamArgs& a, double adam_bytes,
                       hipStream_t s) {
-  const int tm = row_tm(c, c->B), tiles = (c->B + 32 * tm - 1) / (32 * tm);
+  const int tm = row_tm(c, c->B), tiles = row_tile_count(c->B, tm);
   RowWArgs W{};
   RowPArgs p{};
   W.groups = tiles * 32 * tm / row_ks(c);
@@ -1372,7 +1421,7 @@ hipError_t row_act(spz_ctx* c, const float* obs, int n, int64_t row0, bool stoch
   const spz_ctx::RowPlan& P = c->rplan[tm - 1];
   RowArgs g = P.lay;
   g.ops = P.ops;
-  g.tiles = (n + 32 * tm - 1) / (32 * tm);
+  g.tiles = row_tile_count(n, tm);
   g.parts = 1;
   g.op0[0] = P.n_crit + P.n_act;
   g.nops[0] = P.n_sampler;
@@ -1380,7 +1429,7 @@ hipError_t row_act(spz_ctx* c, const float* obs, int n, int64_t row0, bool stoch
   g.seed = c->seed;
   g.lmin = c->hp.log_std_min; g.lmax = c->hp.log_std_max;
   g.obs = obs; g.act = act; g.stochastic = stochastic ? 1 : 0; g.counter = counter; g.row0 = row0;
-  return launch_rows(c->bf16, g, P.max_blocks, P.lds, s);
+  return launch_rows(c->bf16, g, P.lds, s);
 }
 
 FinishArgs finish_args(const spz_ctx* c, int blocks, bool actor_step) {
@@ -1430,8 +1479,7 @@ hipError_t adam(spz_ctx* c, bool critics, bool actor_step, bool actor, int step_
 // The step after the gather on the row-tile path, all on s0 (the two halves of a snapshot
 // step share a launch).
 hipError_t row_enqueue(spz_ctx* c, bool actor_step, bool sequential, hipStream_t s0) {
-  const int tm = row_tm(c, c->B), tiles = (c->B + 32 * tm - 1) / (32 * tm);
-  const FinishArgs f = finish_args(c, tiles, actor_step);
+  const FinishArgs f = finish_args(c, row_tile_count(c->B, row_tm(c, c->B)) * ROW_WAVES, actor_step);
   double bytes = 0.0;
   if (!sequential) {
     HK(row_step(c, true, actor_step, s0));
@@ -1725,9 +1773,10 @@ int setup(spz_ctx* c) {
     const int rc = setup_layers(c);
     if (rc) return rc;
   }
-  // one partial per 256-row block, or per tile of at least 32 rows
-  CK(dalloc_t(c, &c->c_lpart, (size_t)(Bp / 32) * 3 * 8));
-  CK(dalloc_t(c, &c->a_lpart, (size_t)(Bp / 32) * 2 * 8));
+  // one partial per 256-row block, or per wave of a row tile
+  const size_t parts = (size_t)(Bp / ROW_MIN_TILE) * ROW_WAVES;
+  CK(dalloc_t(c, &c->c_lpart, parts * 3 * 8));
+  CK(dalloc_t(c, &c->a_lpart, parts * 2 * 8));
   // streams (default priority)
   CK(hipStreamCreateWithFlags(&c->sc, hipStreamNonBlocking));
   CK(hipStreamCreateWithFlags(&c->sa, hipStreamNonBlocking));

@@ -7,18 +7,17 @@
 namespace spz {
 
 // Everything between the replay gather and the weight gradients is local to a batch row,
-// so a workgroup takes a tile of 32 or 64 rows through a list of operations (RowOp): the
+// so a workgroup takes a tile of 32 (bf16: or 64) rows through a list of operations (RowOp): the
 // layers of the target action, the target and online critics, the losses and the backward
 // chains. Weights come from packed images, activations and output gradients leave as
 // packed images for the weight-gradient product. One 1 KB fragment of a packed image is
 // what one wave feeds to one matrix instruction group: 64 lanes of 16 bytes, lane l = 32 h
 // + r holding
 //   weights        (row r of a 32-row block, k = KS s + KS/2 h + j)   KS = 8 (fp32), 16 (bf16)
-//   batch tensors  (column r of a 32-column block; batch rows 4 h + j (+ 8: bf16's j >= 4)
-//                  of an 8-row (fp32) or 16-row (bf16) group)
-// Fragments of a weight block are consecutive over s; those of a batch tensor consecutive
-// over its column blocks. A batch fragment is four (eight) accumulator registers of the
-// lane that computed them, so producing and consuming it needs no data movement.
+//   batch tensors  (column r of a 32-column block, batch row KS g + KS/2 h + j)
+// Fragments of a weight block are consecutive over the steps s; those of a batch tensor
+// consecutive over its column blocks, then over the row groups g.
+constexpr int ROW_MIN_TILE = 32;
 constexpr int ROW_THREADS = 512, ROW_WAVES = ROW_THREADS / 64;
 constexpr int ROW_MAX_BLOCKS = 4;   // 32-column blocks per wave of one operation
 
@@ -27,17 +26,18 @@ enum RowOpKind : int32_t {
   ROW_OBS,       // sampler observations -> X
   ROW_HIDDEN,    // H = relu(A W^T + b); ReLU mask bits at `mask`; pack: packed image of H
   ROW_Z,         // Z = A W^T + b (actor output)
-  ROW_DGRAD,     // H = (H W) masked by the bits at `mask`; pack; part: column sums
+  ROW_DGRAD,     // H = (H W) masked by the bits at `mask`; pack, part: column sums
   ROW_DACT,      // Z[net] = H W (gradient to the action)
-  ROW_DOT,       // critic output layer: q[net] = H w + b
-  ROW_TARGET,    // TD target
-  ROW_CLOSS,     // critic loss and dq; part: sums of dq
-  ROW_ALOSS,     // actor loss and dq
-  ROW_DZ,        // H = dq w masked by the bits at `mask`; pack; part; wpart: sums of dq h
+  ROW_PACK,      // X or H (from_h) -> packed image; part: column sums
+  ROW_DOT,       // critic output layer: q[net] = H w + b; then by flags: nothing, the TD
+                 // target, the critic loss and dq (part: sums of dq), the actor loss and dq
+  ROW_DZ,        // H = dq w masked by the bits at `mask`; pack, part; before: packed image
+                 // hpack of H (flags 1: there already) and its sums weighted by dq (wpart)
   ROW_HEAD,      // policy head on Z -> action columns of X (flags 1: policy side, 0: target)
-  ROW_HEAD_BWD,  // Z (action gradients) -> actor output gradient in H; pack; part
+  ROW_HEAD_BWD,  // Z (action gradients) -> actor output gradient in H
   ROW_ACT        // sampler actions from Z
 };
+enum RowDotThen : int32_t { ROW_DOT_ONLY, ROW_DOT_TARGET, ROW_DOT_CLOSS, ROW_DOT_ALOSS };
 
 // Operand of two nets where an operation covers both critics (nets = 2: waves 0-3 take net0,
 // waves 4-7 net0 + 1), else of one.
@@ -48,35 +48,36 @@ struct RowOp {
   int32_t from_h;   // A operand: H (else X)
   int32_t mask;     // u16 index into the mask area, -1: none
   int32_t flags;
-  const void* w[2];          // packed weights (ROW_DOT, ROW_DZ: float32 row)
+  int32_t split;    // products: waves per block, each with a range of the steps (a power of two)
+  const void* w[2];          // packed weights (ROW_DOT, ROW_DZ: one row, operand type)
   const float* bias[2];
   void* pack[2];
-  float* part[2];            // [tiles, 32 nblk] (ROW_CLOSS: [tiles])
-  float* wpart[2];           // ROW_DZ: [tiles, 32 nblk]
-  const void* hpack[2];      // ROW_DZ with wpart: packed image of H before it
+  float* part[2];            // [tiles, 32 nblk] (ROW_DOT: [tiles, ROW_WAVES])
+  float* wpart[2];           // [tiles, 32 nblk]
+  void* hpack[2];
 };
-static_assert(sizeof(RowOp) % 8 == 0, "read as 8-byte words");
 
 struct RowArgs {
   const RowOp* ops;
   int op0[2], nops[2];   // operations of the two halves of the grid (critic part, actor part)
   int tiles, parts, B;
   int tm;                // 32-row blocks per tile
-  // LDS: byte offsets, strides in elements (ldx, ldh: operand type; zp: floats)
-  int oX, ldx, oH, ldh, hnet, oZ, zp, oV, oM;
+  // LDS: byte offsets, strides in elements (ldx, ldh: operand type; zp, dp: floats, of the
+  // actor output and of the action gradients in the Z area)
+  int oX, ldx, oH, ldh, hnet, oZ, zp, dp, oV, oM, oS;
   int A, Ka, Ap, Kc, pa, O, sac;
   uint64_t seed; const int64_t* step;
   const void *xsa, *xs2;
   const float *r, *d, *log_alpha;
   float gamma, lmin, lmax, noise, clip;
   float *y, *q1, *q2, *qp1, *qp2, *logp, *th, *se, *lm, *da;
-  double *cpart, *apart;
+  double *cpart, *apart;   // [tiles, ROW_WAVES] loss partials
   // sampler actions
   const float* obs; float* act; int stochastic; uint32_t counter; int64_t row0;
 };
 
-// max_blocks: the most blocks one wave takes in any operation (1 .. ROW_MAX_BLOCKS).
-hipError_t launch_rows(bool bf16, const RowArgs& g, int max_blocks, size_t lds, hipStream_t s);
+// The caller's operations give no wave more than ROW_MAX_BLOCKS blocks.
+hipError_t launch_rows(bool bf16, const RowArgs& g, size_t lds, hipStream_t s);
 
 // Weight gradients from packed images: job j gives part[slice][m block][n block][1024]
 // float32 sums over the slice's row groups, each 32 x 32 block in accumulator order.
@@ -101,7 +102,8 @@ struct RowPBlk {
   int32_t blk;       // kind 0: block index in the job's partials
   int32_t fsteps, tsteps;
   int32_t pad_;
-  int64_t fwd, tr;   // element offsets of the block's fragments in the packed images (tr < 0: none)
+  int64_t fwd, tr;   // element offsets of the block's fragments in the packed images (tr < 0: none);
+                     // kind 1: of the columns' operand image (fwd < 0: none)
   const float* part; // kind 1, 2
 };
 struct RowPJob { const float* part; int64_t zstride; int slices; };

@@ -5,11 +5,12 @@
 // a step, activations written and read back between them. Here a tile's activations stay in
 // LDS and its weights, which every tile shares, stream from L2 as whole 1 KB fragments
 // straight into registers (each fragment is used by one wave only, so LDS would not help).
-// fp32 needs 16 bytes of weights per CU clock at 32-row tiles, far below L2's rate; bf16
-// needs eight times that at 64 rows and is bound by L2.
-// Measured, a step with graph replay against the layer-by-layer path: 2 x 64 fp32 at 256 rows
-// 260 -> 70 us; 2 x 256 fp32 at 8192 rows 520 -> 290 us; 400-300 fp32 (TD3) at 32768 rows
-// 1.89 -> 1.63 ms; 2 x 256 bf16 (376 inputs) at 16384 rows 420 -> 300 us.
+// fp32 is bound by the matrix cores (2 x 256 at 8192 rows: 60% of their rate in k_rows, 400-300
+// at 32768 rows: 77%), bf16 by the weights' way through the vector L1 (64 bytes a clock) and by
+// the fixed time of an operation, 2 - 3 thousand clocks of loads, epilogue and barriers.
+// Measured, a step against the layer-by-layer path: 2 x 64 fp32 at 256 rows 260 -> 53 us; 2 x
+// 256 fp32 at 8192 rows 520 -> 237 us; 400-300 fp32 (TD3) at 32768 rows 1.89 -> 1.45 ms; 2 x
+// 256 bf16 (376 inputs) at 16384 rows 420 -> 198 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 68 us.
 #include "rows.h"
 
 #include <atomic>
@@ -18,13 +19,20 @@ namespace spz {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+#define LDS_AS __attribute__((address_space(3)))
 
+// KS: depth of one step of a product; VEC: elements of 16 bytes; WPB: 32-bit words of 16
+// accumulator values in the operand type.
 template <typename T> struct RowT;
-template <> struct RowT<float> { static constexpr int KS = 8, VEC = 4, RG = 8; };
-template <> struct RowT<bf16_t> { static constexpr int KS = 16, VEC = 8, RG = 16; };
+template <> struct RowT<float> { static constexpr int KS = 8, VEC = 4, WPB = 16; };
+template <> struct RowT<bf16_t> { static constexpr int KS = 16, VEC = 8, WPB = 8; };
 
 // acc += A B^T over one KS-deep step, both operands as fragments.
 template <typename T>
@@ -44,59 +52,88 @@ __device__ inline void zero(f32x16& a) {
   for (int q = 0; q < 16; ++q) a[q] = 0.0f;
 }
 
-// A 32 x 32 block in accumulator order (v: column lane % 32, rows 8 (q / 4) + 4 (lane / 32) +
-// q % 4) to the packed image of a batch tensor with ncb column blocks; rt: 32-row block.
+// A block of a product as a lane holds it: the weight is the A operand, so lane 32 h + r has
+// batch row r and the 16 output columns 8 (q / 4) + 4 h + q % 4 -- four runs of four columns,
+// which go to LDS as 8 (bf16) or 16 bytes each. (The other way round a lane holds 16 rows of
+// one column: 16 two-byte LDS stores and per-value masks took longer than the product itself
+// in bf16.) In the operand type: WPB words, bf16 two columns a word.
+template <typename T> struct Block { uint32_t w[RowT<T>::WPB]; };
+
+__device__ inline uint32_t pk_min1(uint32_t x) {   // min(x, 1) of both halves
+  uint32_t m;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(m) : "v"(x), "s"(0x00010001u));
+  return m;
+}
+
+// ReLU of the accumulators, rounded to the operand type, and its mask: 16 bits, 1 where the
+// stored value is not zero. bf16: the pairs' low halves in bits 7 .. 0, high halves in 15 .. 8.
+// (bf16 drops a negative NaN, as the large-tile kernel's epilogue does; the hardware makes
+// positive ones.)
 template <typename T>
-__device__ inline void pack_block(void* pack, const T (&v)[16], int64_t rt, int ncb, int cb, int lane) {
-  u32x4* p = static_cast<u32x4*>(pack);
-  constexpr int G = 32 / RowT<T>::RG;
+__device__ inline uint32_t relu_block(const f32x16& acc, Block<T>& b) {
+  uint32_t bits = 0;
+  if constexpr (sizeof(T) == 2) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    u32x4 o;
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = (uint32_t)v[8 * g + 2 * e] | ((uint32_t)v[8 * g + 2 * e + 1] << 16);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = __builtin_bit_cast(uint32_t, v[4 * g + e]);
+    for (int p = 0; p < 8; ++p) {
+      const i16x2 v = __builtin_bit_cast(i16x2, pack_bf16x2(acc[2 * p], acc[2 * p + 1]));
+      b.w[p] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, (i16x2){0, 0}));
+      bits = (bits << 1) | pk_min1(b.w[p]);
     }
-    p[((rt * G + g) * ncb + cb) * 64 + lane] = o;
+    bits = __builtin_amdgcn_perm(0u, bits, 0x0C0C0200u);   // bytes 2, 0
+  } else {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const float x = acc[q] < 0.0f ? 0.0f : acc[q];   // keeps NaN
+      b.w[q] = __builtin_bit_cast(uint32_t, x);
+      bits = (bits << 1) | (x > 0.0f ? 1u : 0u);
+    }
+  }
+  return bits;
+}
+
+// v (in the operand type) where the mask bit is set, else 0.
+template <typename T>
+__device__ inline void mask_block(const float (&v)[16], uint32_t bits, Block<T>& b) {
+  if constexpr (sizeof(T) == 2) {
+    const uint32_t m = __builtin_amdgcn_perm(0u, bits, 0x0C010C00u);   // bytes 0 and 1 to the halves
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const uint32_t one = (m >> (7 - p)) & 0x00010001u;
+      b.w[p] = pack_bf16x2(v[2 * p], v[2 * p + 1]) & (one * 0xFFFFu);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) b.w[q] = (bits >> (15 - q)) & 1u ? __builtin_bit_cast(uint32_t, v[q]) : 0u;
   }
 }
 
+// To row-major LDS: p is the lane's row at the block's first column.
 template <typename T>
-__device__ inline void unpack_block(const void* pack, T (&v)[16], int64_t rt, int ncb, int cb, int lane) {
-  const u32x4* p = static_cast<const u32x4*>(pack);
-  constexpr int G = 32 / RowT<T>::RG;
+__device__ inline void store_block(T* p, const Block<T>& b, int half) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const u32x4 o = p[((rt * G + g) * ncb + cb) * 64 + lane];
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[8 * g + 2 * e] = (T)(o[e] & 0xFFFFu);
-        v[8 * g + 2 * e + 1] = (T)(o[e] >> 16);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * g + e] = __builtin_bit_cast(f32x4, o)[e];
-    }
+  for (int g = 0; g < 4; ++g) {
+    if constexpr (sizeof(T) == 2)
+      *reinterpret_cast<uint2*>(p + 8 * g + 4 * half) = make_uint2(b.w[2 * g], b.w[2 * g + 1]);
+    else
+      *reinterpret_cast<u32x4*>(p + 8 * g + 4 * half) = u32x4{b.w[4 * g], b.w[4 * g + 1], b.w[4 * g + 2], b.w[4 * g + 3]};
   }
 }
-
-// Row (within its 32-row block) of accumulator register q.
-__device__ inline int acc_row(int q, int lane) { return 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3); }
 
 // The arguments and the operation list are uniform and constant for the launch: fields are
 // read through the scalar cache where they are used. The pointers are made opaque once per
 // operation, or the compiler would keep every field of both in registers across the whole
-// list and spill them.
+// list and spill them. (The list in LDS and its fields in scalar registers from the start of
+// an operation was slower: the registers spilled, 137 -> 180 us on 2 x 256 bf16, 16384 rows.)
 #define CONST_AS __attribute__((address_space(4)))
 template <typename S>
 __device__ inline const S* opaque(const CONST_AS S* p) {
   asm volatile("" : "+s"(p));
   return (const S*)p;
 }
+
+// Element k (0 or 1) of an operation's pair, without indexed (stack) access.
+template <typename V>
+__device__ inline V pick(const V (&v)[2], int k) { return k ? v[1] : v[0]; }
 
 struct Lds {
   uint8_t* base;
@@ -107,143 +144,260 @@ struct Lds {
   // per-row values: 0, 1 q of the two nets, 2 y, 3, 4 dq of the two nets, 5 log pi
   __device__ inline float* v(int i) const { return reinterpret_cast<float*>(base + g.oV) + i * 32 * g.tm; }
   __device__ inline uint16_t* m() const { return reinterpret_cast<uint16_t*>(base + g.oM); }
+  __device__ inline f32x4* s() const { return reinterpret_cast<f32x4*>(base + g.oS); }
 };
 
-// One product operation on the wave's NB column blocks first, first + stride, ...
-template <typename T, int TM, int MAXNB, int NB>
-__device__ inline void product(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int net, int slot, int first,
-                               int stride, int lane) {
-  constexpr int KS = RowT<T>::KS, BM = 32 * TM;
-  // weight fragments in flight per buffer
-  constexpr int PD = (MAXNB <= 2 && TM == 1 ? 4 : 8) / NB;
-  const int half = lane >> 5, c32 = lane & 31, steps = o.steps;
-  const int lda = o.from_h ? g.ldh : g.ldx;
-  const T* a = (o.from_h ? L.h<T>(slot) : L.x<T>()) + c32 * lda + (KS / 2) * half;
-  const u32x4* w = static_cast<const u32x4*>(o.w[net - o.net0]) + first * steps * 64;
-  const int ws = stride * steps * 64;
-  float bias[NB];
+// Packed image of one 32-column block of X or H (a lane takes a column: bf16 by transposing
+// LDS reads), with its column sums (part) and sums weighted by dq (wpart) over the tile's
+// rows. saved: the image is there already and gives the sums. Reads what other waves wrote
+// only past a barrier; a wave may pack a block that it has just stored.
+template <typename T, int TM>
+__device__ inline void pack_block(const T* src, int ld, int nblk, int cb, int64_t tile, void* image, float* part,
+                                  float* wpart, const float* dq, bool saved, int lane) {
+  constexpr int KS = RowT<T>::KS, G = 32 * TM / KS;
+  const int half = lane >> 5;
+  float sum = 0.0f, wsum = 0.0f;
+  u32x4* dst = static_cast<u32x4*>(image) + (tile * G * nblk + cb) * 64 + lane;
 #pragma unroll
-  for (int j = 0; j < NB; ++j) bias[j] = o.bias[net - o.net0] ? o.bias[net - o.net0][(first + j * stride) * 32 + c32] : 0.0f;
-
-  f32x16 acc[TM][NB];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) zero(acc[i][j]);
-
-  u32x4 b0[PD][NB], b1[PD][NB];
-  auto load = [&](u32x4 (&b)[PD][NB], int s0) {
-#pragma unroll
-    for (int i = 0; i < PD; ++i) {
-      const u32x4* p = w + min(s0 + i, steps - 1) * 64;   // uniform
-#pragma unroll
-      for (int j = 0; j < NB; ++j) b[i][j] = (p + j * ws)[lane];
+  for (int f = 0; f < G; ++f) {
+    u32x4 v;
+    if (saved) {
+      v = dst[f * nblk * 64];
+    } else if constexpr (sizeof(T) == 2) {
+      const int q = lane >> 4, i = lane & 15;
+      const T* p = src + (f * 16 + 8 * (q >> 1) + (i >> 2)) * ld + cb * 32 + 16 * (q & 1) + 4 * (i & 3);
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_AS bf16x4*)(p + 4 * ld));
+      v = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      const T* p = src + (f * 8 + 4 * half) * ld + cb * 32 + (lane & 31);
+      v = __builtin_bit_cast(u32x4, f32x4{p[0], p[ld], p[2 * ld], p[3 * ld]});
     }
-  };
-  auto multiply = [&](const u32x4 (&b)[PD][NB], int s0) {
+    if (!saved) dst[f * nblk * 64] = v;
+    if (part) {
 #pragma unroll
-    for (int i = 0; i < PD; ++i) {
-      if (s0 + i >= steps) break;   // uniform
-      u32x4 af[TM];
-#pragma unroll
-      for (int t = 0; t < TM; ++t) af[t] = *reinterpret_cast<const u32x4*>(a + t * 32 * lda + (s0 + i) * KS);
-#pragma unroll
-      for (int t = 0; t < TM; ++t)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) mma<T>(acc[t][j], af[t], b[i][j]);
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2)
+          sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)v[e]), (bf16x2){1.0f, 1.0f}, sum, false);
+        else
+          sum += __builtin_bit_cast(f32x4, v)[e];
+      }
     }
-  };
-  load(b0, 0);
-  for (int s = 0; s < steps; s += 2 * PD) {
-    if (s + PD < steps) load(b1, s + PD);
-    multiply(b0, s);
-    if (s + 2 * PD < steps) load(b0, s + 2 * PD);
-    if (s + PD < steps) multiply(b1, s + PD);
+    if (wpart) {
+      const float* d = dq + f * KS + KS / 2 * half;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2)   // dq is in the operand type already
+          wsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)v[e]),
+                                                 __builtin_bit_cast(bf16x2, pack_bf16x2(d[2 * e], d[2 * e + 1])), wsum, false);
+        else
+          wsum = fmaf(d[e], __builtin_bit_cast(f32x4, v)[e], wsum);
+      }
+    }
   }
-
-  if (o.from_h) __syncthreads();   // every wave is done reading H before it is overwritten
-  uint16_t* mask = o.mask >= 0 ? L.m() + o.mask + (net - o.net0) * (o.nblk * TM * 64) : nullptr;
-  T* H = L.h<T>(slot);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int cb = first + j * stride, col = cb * 32 + c32;
-    float sum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < TM; ++t) {
-      if (o.kind == ROW_Z || o.kind == ROW_DACT) {
-        float* z = L.z() + (o.kind == ROW_DACT ? (net - 1) * BM * g.zp : 0) + t * 32 * g.zp + col;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) z[acc_row(q, lane) * g.zp] = acc[t][j][q] + bias[j];
-        continue;
-      }
-      T v[16];
-      uint16_t* mp = mask ? mask + (cb * TM + t) * 64 + lane : nullptr;
-      uint32_t bits = 0;
-      if (o.kind == ROW_HIDDEN) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          float x = acc[t][j][q] + bias[j];
-          x = x < 0.0f ? 0.0f : x;
-          v[q] = from_f<T>(x);
-          bits |= to_f<T>(v[q]) > 0.0f ? 1u << q : 0u;
-        }
-        if (mp) *mp = (uint16_t)bits;
-      } else {   // ROW_DGRAD
-        bits = *mp;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          v[q] = from_f<T>((bits >> q) & 1u ? acc[t][j][q] : 0.0f);
-          sum += to_f<T>(v[q]);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) H[(t * 32 + acc_row(q, lane)) * g.ldh + col] = v[q];
-      if (o.pack[net - o.net0]) pack_block<T>(o.pack[net - o.net0], v, tile * TM + t, o.nblk, cb, lane);
-    }
-    if (o.part[net - o.net0]) {
-      sum += __shfl_xor(sum, 32);
-      if (half == 0) o.part[net - o.net0][tile * (o.nblk * 32) + col] = sum;
-    }
+  const int64_t at = tile * (nblk * 32) + cb * 32 + lane;
+  if (part) {
+    sum += __shfl_xor(sum, 32);
+    if (half == 0) part[at] = sum;
+  }
+  if (wpart) {
+    wsum += __shfl_xor(wsum, 32);
+    if (half == 0) wpart[at] = wsum;
   }
 }
 
-// Gradient of the last hidden layer from dq: H = dq w where the unit was active, with its
-// packed image and column sums, and the output layer's weight-gradient sums.
+// One product operation on the wave's NB column blocks first, first + stride, ... over the
+// steps s0 .. s1 - 1. part > 0: the sums go to LDS for the wave with part 0 of the same block.
+template <typename T, int TM, int NB>
+__device__ inline void product(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int net, int slot, int first,
+                               int stride, int part, int group, int lane) {
+  constexpr int KS = RowT<T>::KS;
+  // Steps of weights in flight: a ring, each slot reloaded as soon as it is used (12 or 16
+  // fragments instead of 8 gain nothing, 24 cost 4% on 400-300 fp32).
+  constexpr int PD = 8 / NB;
+  const int half = lane >> 5, r = lane & 31, k = net - o.net0;
+  const int lda = o.from_h ? g.ldh : g.ldx;
+  const int s0 = o.steps * part / o.split, s1 = o.steps * (part + 1) / o.split;
+  const T* a = (o.from_h ? L.h<T>(slot) : L.x<T>()) + r * lda + (KS / 2) * half;
+  const u32x4* w = static_cast<const u32x4*>(pick(o.w, k)) + first * o.steps * 64;
+  const int ws = stride * o.steps * 64;
+  u32x4 b[PD][NB];
+  auto load = [&](int i, int s) {
+    const u32x4* p = w + min(s, s1 - 1) * 64;   // uniform
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[i][j] = (p + j * ws)[lane];
+  };
+  f32x16 acc[TM][NB];
+  auto multiply = [&](int i, int s) {
+    u32x4 x[TM];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) x[t] = *reinterpret_cast<const u32x4*>(a + t * 32 * lda + s * KS);
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int t = 0; t < TM; ++t) mma<T>(acc[t][j], b[i][j], x[t]);
+  };
+  // bf16: the bias starts the accumulators. fp32 adds it last, as the layer-by-layer products
+  // do: both paths' pre-activations are the same bits, and so are their ReLU decisions.
+  constexpr bool BIAS_FIRST = sizeof(T) == 2;
+  const float* bias = part == 0 ? pick(o.bias, k) : nullptr;
+  auto bias_run = [&](int j, int q) {
+    return *reinterpret_cast<const f32x4*>(bias + (first + j * stride) * 32 + 8 * q + 4 * half);
+  };
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    zero(acc[0][j]);
+    if (BIAS_FIRST && bias) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = bias_run(j, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][j][4 * q + e] = v[e];
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PD; ++i) load(i, s0 + i);
+#pragma unroll
+  for (int t = 1; t < TM; ++t)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[t][j] = acc[0][j];
+  int s = s0;
+  for (; s + PD < s1; s += PD) {
+#pragma unroll
+    for (int i = 0; i < PD; ++i) {
+      multiply(i, s + i);
+      load(i, s + PD + i);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PD; ++i) {
+    if (s + i >= s1) break;   // uniform
+    multiply(i, s + i);
+  }
+
+  if (!BIAS_FIRST && bias) {
+    static_assert(BIAS_FIRST || TM == 1, "one row block");
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = bias_run(j, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][j][4 * q + e] += v[e];
+      }
+  }
+
+  if (o.split > 1) {   // one block per wave
+    f32x4* buf = L.s() + group * (o.split - 1) * (256 * TM) + lane;
+    if (part > 0) {
+#pragma unroll
+      for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          buf[((part - 1) * TM + t) * 256 + q * 64] =
+              f32x4{acc[t][0][4 * q], acc[t][0][4 * q + 1], acc[t][0][4 * q + 2], acc[t][0][4 * q + 3]};
+    }
+    __syncthreads();
+    if (part > 0) return;
+    for (int p = 0; p < o.split - 1; ++p)
+#pragma unroll
+      for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = buf[(p * TM + t) * 256 + q * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[t][0][4 * q + e] += v[e];
+        }
+  } else if (o.from_h) {
+    __syncthreads();   // every wave is done reading H before it is overwritten
+  }
+  if (o.kind == ROW_Z || o.kind == ROW_DACT) {
+    const int zp = o.kind == ROW_DACT ? g.dp : g.zp;
+    float* z = L.z() + (o.kind == ROW_DACT ? (net - 1) * 32 * TM * zp : 0) + r * zp;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(z + t * 32 * zp + (first + j * stride) * 32 + 8 * q + 4 * half) =
+              f32x4{acc[t][j][4 * q], acc[t][j][4 * q + 1], acc[t][j][4 * q + 2], acc[t][j][4 * q + 3]};
+    return;
+  }
+  uint16_t* mask = L.m() + o.mask + k * (o.nblk * TM * 64) + lane;
+  T* H = L.h<T>(slot) + r * g.ldh;
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      const int cb = first + j * stride;
+      uint16_t* m = mask + (cb * TM + t) * 64;
+      Block<T> v;
+      if (o.kind == ROW_HIDDEN) {
+        const uint32_t bits = relu_block<T>(acc[t][j], v);
+        if (o.mask >= 0) *m = (uint16_t)bits;
+      } else {   // ROW_DGRAD
+        float x[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[q] = acc[t][j][q];
+        mask_block<T>(x, *m, v);
+      }
+      store_block<T>(H + t * 32 * g.ldh + cb * 32, v, half);
+    }
+  if (pick(o.pack, k)) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      pack_block<T, TM>(L.h<T>(slot), g.ldh, o.nblk, first + j * stride, tile, pick(o.pack, k), pick(o.part, k), nullptr,
+                        nullptr, false, lane);
+  }
+}
+
+// Gradient of the last hidden layer from dq: H = dq w where the unit was active. For the
+// critics' own gradients its packed image and column sums, and before it is overwritten the
+// packed image of H with the output layer's weight-gradient sums (saved: the image is there).
 template <typename T, int TM>
 __device__ inline void output_backward(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int net, int slot,
                                        int first, int cnt, int stride, int lane) {
-  const int k = net - o.net0, c32 = lane & 31;
-  const uint16_t* mask = L.m() + o.mask + k * (o.nblk * TM * 64);
-  const float* dq = L.v(3 + net - 1);
-  T* H = L.h<T>(slot);
+  const int k = net - o.net0, half = lane >> 5, r = lane & 31;
+  const uint16_t* mask = L.m() + o.mask + k * (o.nblk * TM * 64) + lane;
+  const float* dq = L.v(3 + net - 1) + r;
+  const T* w = static_cast<const T*>(pick(o.w, k));
+  T* H = L.h<T>(slot) + r * g.ldh;
   for (int j = 0; j < cnt; ++j) {
-    const int cb = first + j * stride, col = cb * 32 + c32;
-    const float w = to_f<T>(from_f<T>(static_cast<const float*>(o.w[k])[col]));
-    float sum = 0.0f, wsum = 0.0f;
+    const int cb = first + j * stride;
+    if (pick(o.hpack, k))
+      pack_block<T, TM>(L.h<T>(slot), g.ldh, o.nblk, cb, tile, pick(o.hpack, k), nullptr, pick(o.wpart, k),
+                        L.v(3 + net - 1), o.flags != 0, lane);
+    float wf[16];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const T* p = w + cb * 32 + 8 * q + 4 * half;
+      if constexpr (sizeof(T) == 2) {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        wf[4 * q] = bf2f((bf16_t)(v.x & 0xFFFFu));
+        wf[4 * q + 1] = bf2f((bf16_t)(v.x >> 16));
+        wf[4 * q + 2] = bf2f((bf16_t)(v.y & 0xFFFFu));
+        wf[4 * q + 3] = bf2f((bf16_t)(v.y >> 16));
+      } else {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wf[4 * q + e] = v[e];
+      }
+    }
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
-      const uint32_t bits = mask[(cb * TM + t) * 64 + lane];
-      T v[16], h[16];
-      if (o.wpart[k]) unpack_block<T>(o.hpack[k], h, tile * TM + t, o.nblk, cb, lane);
+      const float d = dq[t * 32];
+      float x[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int r = t * 32 + acc_row(q, lane);
-        const float d = dq[r];
-        if (o.wpart[k]) wsum = fmaf(d, to_f<T>(h[q]), wsum);
-        v[q] = from_f<T>((bits >> q) & 1u ? d * w : 0.0f);
-        sum += to_f<T>(v[q]);
-        H[r * g.ldh + col] = v[q];
-      }
-      if (o.pack[k]) pack_block<T>(o.pack[k], v, tile * TM + t, o.nblk, cb, lane);
+      for (int q = 0; q < 16; ++q) x[q] = d * wf[q];
+      Block<T> v;
+      mask_block<T>(x, mask[(cb * TM + t) * 64], v);
+      store_block<T>(H + t * 32 * g.ldh + cb * 32, v, half);
     }
-    if (o.part[k]) {
-      sum += __shfl_xor(sum, 32);
-      if (lane < 32) o.part[k][tile * (o.nblk * 32) + col] = sum;
-    }
-    if (o.wpart[k]) {
-      wsum += __shfl_xor(wsum, 32);
-      if (lane < 32) o.wpart[k][tile * (o.nblk * 32) + col] = wsum;
-    }
+    if (pick(o.pack, k))
+      pack_block<T, TM>(L.h<T>(slot), g.ldh, o.nblk, cb, tile, pick(o.pack, k), pick(o.part, k), nullptr, nullptr, false,
+                        lane);
   }
 }
 
@@ -258,135 +412,137 @@ __device__ inline void load_tile(const RowArgs& g, const RowOp& o, const Lds& L,
     const int r = v / nv, c = (v - r * nv) * VEC;
     *reinterpret_cast<u32x4*>(X + r * g.ldx + c) = *reinterpret_cast<const u32x4*>(src + (int64_t)v * VEC);
   }
-  if (!o.pack[0]) return;
-  __syncthreads();
-  const int lane = tid & 63, ncb = g.Kc / 32;
-  for (int u = tid >> 6; u < ncb * TM; u += ROW_WAVES) {
-    const int cb = u % ncb, t = u / ncb;
-    T v[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) v[q] = X[(t * 32 + acc_row(q, lane)) * g.ldx + cb * 32 + (lane & 31)];
-    pack_block<T>(o.pack[0], v, tile * TM + t, ncb, cb, lane);
-  }
 }
 
-// q[net][r] of the critic output layer: 16 lanes per row.
+// Sum over the wave's groups of LPR lanes (every lane of a group holds its value).
+template <int LPR, typename V>
+__device__ inline V group_sum(V v) {
+#pragma unroll
+  for (int m = LPR; m < 64; m <<= 1) v += __shfl_xor(v, m);
+  return v;
+}
+
+// The critic output layer, LPR lanes per row of the tile, and what follows from q per row:
+//   target       y = r + gamma (1 - d) (min(q1, q2) - alpha log pi)
+//   critic loss  dq_i = 2 (q_i - y) / B in the operand type; sums of (q1 - y)^2, (q2 - y)^2,
+//                q1 and each dq per wave
+//   actor loss   SAC: dq = -1 / B to the smaller critic (critic 1 on ties), sums of
+//                alpha log pi - min(q1, q2) and log pi; TD3: critic 1 only, sum of q1
+// One operation, so that neither q nor y waits for a barrier of its own.
 template <typename T, int TM>
-__device__ inline void output_dot(const RowArgs& g, const RowOp& o, const Lds& L, int tid) {
-  constexpr int VEC = RowT<T>::VEC, BM = 32 * TM;
-  const int l = tid & 15, K = o.nblk * 32;
-  for (int d = tid >> 4; d < o.nets * BM; d += ROW_THREADS / 16) {
-    const int k = d / BM, r = d % BM;
-    const T* h = L.h<T>(o.nets == 2 ? k : 0) + r * g.ldh;
-    const float* w = static_cast<const float*>(k ? o.w[1] : o.w[0]);
+__device__ inline void output_dot(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int tid) {
+  constexpr int VEC = RowT<T>::VEC, LPR = ROW_THREADS / (32 * TM);
+  const int l = tid % LPR, r = tid / LPR, K = o.nblk * 32;
+  const int64_t b = tile * (32 * TM) + r;
+  const bool live = b < g.B;
+  float rew = 0.0f, done = 0.0f;
+  if (o.flags == ROW_DOT_TARGET && live) {
+    rew = g.r[b];
+    done = g.d[b];
+  }
+  float q[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (k >= o.nets) break;
+    const T* h = L.h<T>(k) + r * g.ldh;
+    const T* w = static_cast<const T*>(k ? o.w[1] : o.w[0]);
     float s = 0.0f;
-    for (int c = l * VEC; c < K; c += 16 * VEC) {
-      const u32x4 hv = *reinterpret_cast<const u32x4*>(h + c);
+#pragma unroll 4
+    for (int c = l * VEC; c < K; c += LPR * VEC) {
+      const u32x4 hv = *reinterpret_cast<const u32x4*>(h + c), wv = *reinterpret_cast<const u32x4*>(w + c);
 #pragma unroll
-      for (int e = 0; e < VEC / 4; ++e) {
-        const f32x4 wv = *reinterpret_cast<const f32x4*>(w + c + 4 * e);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float hx;
-          if constexpr (sizeof(T) == 2) {
-            const uint32_t p = hv[2 * e + (i >> 1)];
-            hx = bf2f((bf16_t)(i & 1 ? p >> 16 : p & 0xFFFFu));
-          } else {
-            hx = __builtin_bit_cast(f32x4, hv)[i];
-          }
-          s = fmaf(hx, to_f<T>(from_f<T>(wv[i])), s);
-        }
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2)
+          s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)hv[e]),
+                                              __builtin_bit_cast(bf16x2, (uint32_t)wv[e]), s, false);
+        else
+          s = fmaf(__builtin_bit_cast(f32x4, hv)[e], __builtin_bit_cast(f32x4, wv)[e], s);
       }
     }
 #pragma unroll
-    for (int m = 8; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    if (l == 0) L.v(o.net0 - 1 + k)[r] = s + *(k ? o.bias[1] : o.bias[0]);
+    for (int m = LPR / 2; m > 0; m >>= 1) s += __shfl_xor(s, m);
+    q[k] = s + *(k ? o.bias[1] : o.bias[0]);
   }
-}
-
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
-  return v;
-}
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
-  return v;
-}
-
-// Critic loss of the tile's rows (the first wave): dq_i = 2 (q_i - y) / B in the operand
-// type, and the tile's sums of (q1 - y)^2, (q2 - y)^2, q1 and of each dq.
-template <typename T, int TM>
-__device__ inline void critic_loss(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int lane) {
-  constexpr int BM = 32 * TM;
-  const int64_t b = tile * BM + lane;
+  if (o.flags == ROW_DOT_ONLY) {   // critic 1 of two that run one after the other
+    if (l == 0) L.v(0)[r] = q[0];
+    return;
+  }
+  if (o.nets == 1 && o.net0 == 2) {
+    q[1] = q[0];
+    q[0] = L.v(0)[r];
+  }
+  const bool first = l == 0;
+  if (o.flags == ROW_DOT_TARGET) {
+    float m = min_keep_nan(q[0], q[1]);
+    if (g.sac) m -= expf(*g.log_alpha) * L.v(5)[r];
+    const float y = live ? rew + g.gamma * (1.0f - done) * m : 0.0f;
+    if (first) L.v(2)[r] = y;
+    if (first && live) g.y[b] = y;
+    return;
+  }
+  const int64_t at = tile * ROW_WAVES + (tid >> 6);
   float d1 = 0.0f, d2 = 0.0f;
-  double e1s = 0.0, e2s = 0.0, q1s = 0.0;
-  if (lane < BM) {
-    if (b < g.B) {
-      const float q1 = L.v(0)[lane], q2 = L.v(1)[lane], y = L.v(2)[lane];
-      const float e1 = q1 - y, e2 = q2 - y;
+  if (o.flags == ROW_DOT_CLOSS) {
+    double e1s = 0.0, e2s = 0.0, q1s = 0.0;
+    if (live) {
+      const float y = L.v(2)[r];
+      const float e1 = q[0] - y, e2 = q[1] - y;
       d1 = to_f<T>(from_f<T>(2.0f * e1 / (float)g.B));
       d2 = to_f<T>(from_f<T>(2.0f * e2 / (float)g.B));
       e1s = (double)e1 * e1;
       e2s = (double)e2 * e2;
-      q1s = q1;
-      g.q1[b] = q1;
-      g.q2[b] = q2;
+      q1s = q[0];
     }
-    L.v(3)[lane] = d1;
-    L.v(4)[lane] = d2;
+    if (first && live) {
+      g.q1[b] = q[0];
+      g.q2[b] = q[1];
+    }
+    if (first) {
+      L.v(3)[r] = d1;
+      L.v(4)[r] = d2;
+    }
+    e1s = group_sum<LPR>(e1s);
+    e2s = group_sum<LPR>(e2s);
+    q1s = group_sum<LPR>(q1s);
+    d1 = group_sum<LPR>(d1);
+    d2 = group_sum<LPR>(d2);
+    if ((tid & 63) == 0) {
+      g.cpart[at * 3 + 0] = e1s;
+      g.cpart[at * 3 + 1] = e2s;
+      g.cpart[at * 3 + 2] = q1s;
+      o.part[0][at] = d1;
+      o.part[1][at] = d2;
+    }
+    return;
   }
-  e1s = wave_sum(e1s);
-  e2s = wave_sum(e2s);
-  q1s = wave_sum(q1s);
-  d1 = wave_sum(d1);
-  d2 = wave_sum(d2);
-  if (lane == 0) {
-    g.cpart[tile * 3 + 0] = e1s;
-    g.cpart[tile * 3 + 1] = e2s;
-    g.cpart[tile * 3 + 2] = q1s;
-    o.part[0][tile] = d1;
-    o.part[1][tile] = d2;
-  }
-}
-
-// Actor loss of the tile's rows (the first wave). SAC: dq = -1 / B to the smaller critic
-// (critic 1 on ties); sums of alpha log pi - min(q1, q2) and of log pi. TD3: critic 1 only,
-// sum of q1.
-template <typename T, int TM>
-__device__ inline void actor_loss(const RowArgs& g, const Lds& L, int64_t tile, int lane) {
-  constexpr int BM = 32 * TM;
-  const int64_t b = tile * BM + lane;
   double l0 = 0.0, l1 = 0.0;
-  if (lane < BM) {
-    float g1 = 0.0f, g2 = 0.0f;
-    if (b < g.B) {
-      const float inv = to_f<T>(from_f<T>(-1.0f / (float)g.B));
-      const float q1 = L.v(0)[lane];
-      g.qp1[b] = q1;
-      if (g.sac) {
-        const float q2 = L.v(1)[lane], lp = L.v(5)[lane];
-        const bool take1 = q1 <= q2;
-        g1 = take1 ? inv : 0.0f;
-        g2 = take1 ? 0.0f : inv;
-        l0 = (double)expf(*g.log_alpha) * lp - (double)(take1 ? q1 : q2);
-        l1 = lp;
-        g.qp2[b] = q2;
-      } else {
-        g1 = inv;
-        l0 = q1;
-      }
+  if (live) {
+    const float inv = to_f<T>(from_f<T>(-1.0f / (float)g.B));
+    if (g.sac) {
+      const float lp = L.v(5)[r];
+      const bool take1 = q[0] <= q[1];
+      d1 = take1 ? inv : 0.0f;
+      d2 = take1 ? 0.0f : inv;
+      l0 = (double)expf(*g.log_alpha) * lp - (double)(take1 ? q[0] : q[1]);
+      l1 = lp;
+    } else {
+      d1 = inv;
+      l0 = q[0];
     }
-    L.v(3)[lane] = g1;
-    L.v(4)[lane] = g2;
   }
-  l0 = wave_sum(l0);
-  l1 = wave_sum(l1);
-  if (lane == 0) {
-    g.apart[tile * 2 + 0] = l0;
-    g.apart[tile * 2 + 1] = l1;
+  if (first && live) {
+    g.qp1[b] = q[0];
+    if (g.sac) g.qp2[b] = q[1];
+  }
+  if (first) {
+    L.v(3)[r] = d1;
+    L.v(4)[r] = d2;
+  }
+  l0 = group_sum<LPR>(l0);
+  l1 = group_sum<LPR>(l1);
+  if ((tid & 63) == 0) {
+    g.apart[at * 2 + 0] = l0;
+    g.apart[at * 2 + 1] = l1;
   }
 }
 
@@ -436,56 +592,46 @@ __device__ inline void head(const RowArgs& g, const RowOp& o, const Lds& L, int6
 }
 
 // Actor head backward: the action gradients in Z (of both critics for SAC) -> the actor's
-// output gradient in H, with its packed image and column sums.
+// output gradient in H.
 template <typename T, int TM>
 __device__ inline void head_backward(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int tid) {
   constexpr int BM = 32 * TM;
   T* H = L.h<T>(0);
   const float* D = L.z();
   const float aB = g.sac ? expf(*g.log_alpha) / (float)g.B : 0.0f;
-  for (int e = tid; e < BM * g.pa; e += ROW_THREADS) {
-    const int r = e / g.pa, c = e - r * g.pa;
+  // both outputs of an (row, action) element; the columns past the outputs are zero
+  for (int e = tid; e < BM * g.A; e += ROW_THREADS) {
+    const int r = e / g.A, j = e - r * g.A;
     const int64_t b = tile * BM + r;
-    const bool mean = c < g.A;
-    const int j = mean ? c : c - g.A;
-    float out = 0.0f;
-    if (b < g.B && (mean || (g.sac && j < g.A))) {
-      float da = D[r * g.zp + j];
-      if (g.sac) da += D[(BM + r) * g.zp + j];
+    float gm = 0.0f, gl = 0.0f;
+    if (b < g.B) {
       const uint64_t i = (uint64_t)b * g.A + j;
       const float a = g.th[i];
-      out = da * (1.0f - a * a);
-      if (g.sac) out += aB * 2.0f * a;
-      if (mean) g.da[b * g.Ap + j] = da;
-      else out = (out * g.se[i] - aB) * g.lm[i];
-    }
-    H[r * g.ldh + c] = from_f<T>(out);
-  }
-  __syncthreads();
-  const int lane = tid & 63;
-  for (int cb = tid >> 6; cb < o.nblk; cb += ROW_WAVES) {
-    float sum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < TM; ++t) {
-      T v[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        v[q] = H[(t * 32 + acc_row(q, lane)) * g.ldh + cb * 32 + (lane & 31)];
-        sum += to_f<T>(v[q]);
+      float da = D[r * g.dp + j];
+      if (g.sac) {
+        const float se = g.se[i], lm = g.lm[i];
+        da += D[(BM + r) * g.dp + j];
+        gm = da * (1.0f - a * a) + aB * 2.0f * a;
+        gl = (gm * se - aB) * lm;
+      } else {
+        gm = da * (1.0f - a * a);
       }
-      pack_block<T>(o.pack[0], v, tile * TM + t, o.nblk, cb, lane);
+      g.da[b * g.Ap + j] = da;
     }
-    sum += __shfl_xor(sum, 32);
-    if (lane < 32) o.part[0][tile * (o.nblk * 32) + cb * 32 + lane] = sum;
+    H[r * g.ldh + j] = from_f<T>(gm);
+    if (g.sac) H[r * g.ldh + g.A + j] = from_f<T>(gl);
   }
+  const int used = g.sac ? 2 * g.A : g.A, rest = g.pa - used;
+  for (int e = tid; e < BM * rest; e += ROW_THREADS) H[e / rest * g.ldh + used + e % rest] = from_f<T>(0.0f);
 }
 
-template <typename T, int TM, int MAXNB>
-__global__ void __launch_bounds__(ROW_THREADS, MAXNB <= 2 && TM == 1 ? 4 : 2) k_rows(RowArgs args) {
+// 32-row tiles: 128 registers, two workgroups per CU where their LDS allows it; 64-row tiles
+// take the LDS of a CU.
+template <typename T, int TM>
+__global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs args) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int BM = 32 * TM;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = (int)blockIdx.x >= args.tiles ? 1 : 0;
   const int64_t tile = (int)blockIdx.x - part * args.tiles;
   const CONST_AS RowArgs* argp = (const CONST_AS RowArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -493,20 +639,34 @@ __global__ void __launch_bounds__(ROW_THREADS, MAXNB <= 2 && TM == 1 ? 4 : 2) k_
   for (int n = args.nops[part]; n > 0; --n, ++op) {
     const RowArgs& g = *opaque(argp);
     const RowOp& o = *opaque(op);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (as for the pointers: no per-lane values kept across operations)
+    const int lane = tid & 63;
     const Lds L{smem, g};
-    // The wave's share of the operation's column blocks.
+    // The wave's share of the operation's column blocks: blocks first, first + wpn, ... of
+    // one net, or (split) a range of the steps of one block.
     const int wpn = o.nets == 2 ? ROW_WAVES / 2 : ROW_WAVES;
-    const int k = wave / wpn, first = wave - k * wpn;
+    const int k = wave / wpn, i = wave - k * wpn;
     const int net = o.net0 + k, slot = o.nets == 2 ? k : 0;
-    const int cnt = o.nblk > first ? (o.nblk - 1 - first) / wpn + 1 : 0;
+    // Blocks of the second net start at the other end: with few blocks both nets' waves
+    // would otherwise share matrix cores (wave w runs on SIMD w % 4).
+    const int turn = k ? wpn - 1 - i : i;
+    int first = turn, kpart = 0;
+    if (o.split > 1) {
+      first = turn % o.nblk;
+      kpart = turn / o.nblk;
+    }
+    const int cnt = o.split > 1 ? (kpart < o.split ? 1 : 0) : o.nblk > first ? (o.nblk - 1 - first) / wpn + 1 : 0;
     switch (o.kind) {
-      case ROW_HIDDEN: case ROW_Z: case ROW_DGRAD: case ROW_DACT:
-        if (cnt == 1) product<T, TM, MAXNB, 1>(g, o, L, tile, net, slot, first, wpn, lane);
-        else if (cnt == 2) product<T, TM, MAXNB, 2>(g, o, L, tile, net, slot, first, wpn, lane);
-        else if (MAXNB > 2 && cnt == 3) product<T, TM, MAXNB, (MAXNB > 2 ? 3 : 1)>(g, o, L, tile, net, slot, first, wpn, lane);
-        else if (MAXNB > 2 && cnt == 4) product<T, TM, MAXNB, (MAXNB > 2 ? 4 : 1)>(g, o, L, tile, net, slot, first, wpn, lane);
-        else if (o.from_h) __syncthreads();
+      case ROW_HIDDEN: case ROW_Z: case ROW_DGRAD: case ROW_DACT: {
+        const int group = slot * o.nblk + first;
+        if (cnt == 1) product<T, TM, 1>(g, o, L, tile, net, slot, first, wpn, kpart, group, lane);
+        else if (cnt == 2) product<T, TM, 2>(g, o, L, tile, net, slot, first, wpn, 0, group, lane);
+        else if (cnt == 3) product<T, TM, 3>(g, o, L, tile, net, slot, first, wpn, 0, group, lane);
+        else if (cnt == 4) product<T, TM, 4>(g, o, L, tile, net, slot, first, wpn, 0, group, lane);
+        else if (o.split > 1 || o.from_h) __syncthreads();
         break;
+      }
       case ROW_LOAD: load_tile<T, TM>(g, o, L, tile, tid); break;
       case ROW_OBS: {
         T* X = L.x<T>();
@@ -517,24 +677,13 @@ __global__ void __launch_bounds__(ROW_THREADS, MAXNB <= 2 && TM == 1 ? 4 : 2) k_
         }
         break;
       }
-      case ROW_DOT: output_dot<T, TM>(g, o, L, tid); break;
-      case ROW_TARGET:
-        if (tid < BM) {
-          const int64_t b = tile * BM + tid;
-          float y = 0.0f;
-          if (b < g.B) {
-            const float q1 = L.v(0)[tid], q2 = L.v(1)[tid];
-            float m = min_keep_nan(q1, q2);
-            if (g.sac) m -= expf(*g.log_alpha) * L.v(5)[tid];
-            y = g.r[b] + g.gamma * (1.0f - g.d[b]) * m;
-            g.y[b] = y;
-          }
-          L.v(2)[tid] = y;
-        }
-        break;
-      case ROW_CLOSS: if (wave == 0) critic_loss<T, TM>(g, o, L, tile, lane); break;
-      case ROW_ALOSS: if (wave == 0) actor_loss<T, TM>(g, L, tile, lane); break;
+      case ROW_DOT: output_dot<T, TM>(g, o, L, tile, tid); break;
       case ROW_DZ: output_backward<T, TM>(g, o, L, tile, net, slot, first, cnt, wpn, lane); break;
+      case ROW_PACK:
+        for (int cb = wave; cb < o.nblk; cb += ROW_WAVES)
+          pack_block<T, TM>(o.from_h ? L.h<T>(0) : L.x<T>(), o.from_h ? g.ldh : g.ldx, o.nblk, cb, tile, o.pack[0],
+                            o.part[0], nullptr, nullptr, false, lane);
+        break;
       case ROW_HEAD: head<T, TM>(g, o, L, tile, tid); break;
       case ROW_HEAD_BWD: head_backward<T, TM>(g, o, L, tile, tid); break;
       case ROW_ACT:
@@ -551,7 +700,7 @@ __global__ void __launch_bounds__(ROW_THREADS, MAXNB <= 2 && TM == 1 ? 4 : 2) k_
         }
         break;
     }
-    __syncthreads();
+    if (o.kind != ROW_PACK) __syncthreads();   // what a pack reads is overwritten only past a later barrier
   }
 }
 
@@ -667,6 +816,10 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   // Thread of a weight block: column n, rows m0 .. m0 + 3 (accumulator order).
   const int lane = tid & 63, n = lane & 31, m0 = 8 * (tid >> 6) + 4 * (lane >> 5);
   if (!p.update) {
+    if (B.kind == 1 && B.fwd >= 0 && tid < 16) {
+      PF[B.fwd + tid] = from_f<T>(a.P[B.off + tid]);
+      TF[B.fwd + tid] = from_f<T>(a.T[B.off + tid]);
+    }
     if (B.kind != 0) return;
     float v[4], u[4];
 #pragma unroll
@@ -733,13 +886,17 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     const float* f = reinterpret_cast<const float*>(sh);
     float g = 0.0f;
     for (int q = 0; q < 64; ++q) g += f[q * 16 + tid];
-    element(B.off + tid, g, t);
+    const float x = element(B.off + tid, g, t);
+    if (B.fwd >= 0) {
+      PF[B.fwd + tid] = from_f<T>(x);
+      if (polyak) TF[B.fwd + tid] = from_f<T>(t);
+    }
     return;
   }
   if (B.kind == 2) {
     float* f = reinterpret_cast<float*>(sh);
     float s = 0.0f;
-    for (int z = tid; z < p.vslices; z += 256) s += B.part[z];
+    for (int z = tid; z < p.vslices * ROW_WAVES; z += 256) s += B.part[z];
     f[tid] = s;
     __syncthreads();
     if (tid != 0) return;
@@ -757,28 +914,27 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   }
 }
 
-template <typename T, int TM, int MAXNB>
+template <typename T, int TM>
 hipError_t launch_rows_t(const RowArgs& g, size_t lds, hipStream_t s) {
   static std::atomic<bool> ready{false};
   if (!ready.load()) {
-    const hipError_t e = hipFuncSetAttribute((const void*)(k_rows<T, TM, MAXNB>),
+    const hipError_t e = hipFuncSetAttribute((const void*)(k_rows<T, TM>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     ready.store(true);
   }
-  (k_rows<T, TM, MAXNB>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
+  (k_rows<T, TM>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_rows(bool bf16, const RowArgs& g, int max_blocks, size_t lds, hipStream_t s) {
-  if (g.tiles < 1 || g.parts < 1 || g.parts > 2 || (g.tm != 1 && g.tm != 2) || max_blocks < 1 ||
-      max_blocks > ROW_MAX_BLOCKS || lds > 160 * 1024 || (!bf16 && g.tm != 1) || (int64_t)g.tiles * 32 * g.tm < g.B)
+hipError_t launch_rows(bool bf16, const RowArgs& g, size_t lds, hipStream_t s) {
+  if (g.tiles < 1 || g.parts < 1 || g.parts > 2 || lds > 160 * 1024 || (g.tm != 1 && g.tm != 2) ||
+      (!bf16 && g.tm != 1) || (int64_t)g.tiles * 32 * g.tm < g.B)
     return hipErrorInvalidValue;
-  if (!bf16) return max_blocks <= 2 ? launch_rows_t<float, 1, 2>(g, lds, s) : launch_rows_t<float, 1, 4>(g, lds, s);
-  if (g.tm == 1) return max_blocks <= 2 ? launch_rows_t<bf16_t, 1, 2>(g, lds, s) : launch_rows_t<bf16_t, 1, 4>(g, lds, s);
-  return max_blocks <= 2 ? launch_rows_t<bf16_t, 2, 2>(g, lds, s) : launch_rows_t<bf16_t, 2, 4>(g, lds, s);
+  if (!bf16) return launch_rows_t<float, 1>(g, lds, s);
+  return g.tm == 1 ? launch_rows_t<bf16_t, 1>(g, lds, s) : launch_rows_t<bf16_t, 2>(g, lds, s);
 }
 
 hipError_t launch_row_wgrad(bool bf16, RowWArgs& w, hipStream_t s) {
