@@ -113,6 +113,10 @@ struct spz_ctx {
   int64_t row_bytes = 0, cap = 0, ptr = 0, size = 0;
   int off_a = 0, off_s2 = 0, off_r = 0, off_d = 0;
   float* stage = nullptr;
+  // Pinned host memory for small results and inputs: kernels read and write it in place, so a
+  // call waits once for its launch and for no copies (two copies of a few KB through pageable
+  // memory take 30 us, a launch and its wait 12).
+  uint8_t* pin = nullptr;
   // asynchronous ingestion: pinned host slots copied to device slots on their own
   // stream, committed into the ring on the update stream
   struct IngestSlot { float* host = nullptr; float* dev = nullptr; hipEvent_t copied = nullptr, done = nullptr; bool used = false; };
@@ -203,6 +207,8 @@ struct spz_ctx {
   bool has_last = false;   // an update was enqueued on `last` (which may be the null stream)
   std::vector<void*> cs_hid, cs_hid2;   // ping-pong views of cs_h, cs_h2, one entry per hidden layer
   std::vector<void*> allocs;
+  uint8_t* slab = nullptr;       // rest of the current slab of small buffers
+  size_t slab_left = 0;
   // kernel timing
   struct ProfKey { std::string name; int M, N, K; double flops, bytes; int64_t launches; double ms; };
   struct ProfEv { int key; hipEvent_t a, b; };
@@ -242,12 +248,27 @@ int fail_hip(spz_ctx* c, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return e_;        \
   } while (0)
 
+// Zeroed device memory that lives as long as the context. Small buffers share slabs: an
+// allocation and its clearing take some 10 us each, a context has up to a hundred.
+constexpr size_t SLAB_BYTES = (size_t)4 << 20;
 hipError_t dalloc(spz_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
-  if (bytes == 0) bytes = 256;
-  HK(hipMalloc(p, bytes));
+  bytes = std::max<size_t>((bytes + 255) / 256 * 256, 256);
+  const bool small = bytes <= SLAB_BYTES / 8;
+  if (small && c->slab_left >= bytes) {
+    *p = c->slab;
+    c->slab += bytes;
+    c->slab_left -= bytes;
+    return hipSuccess;
+  }
+  const size_t n = small ? SLAB_BYTES : bytes;
+  HK(hipMalloc(p, n));
   c->allocs.push_back(*p);
-  return hipMemset(*p, 0, bytes);
+  if (small) {
+    c->slab = static_cast<uint8_t*>(*p) + bytes;
+    c->slab_left = n - bytes;
+  }
+  return hipMemset(*p, 0, n);
 }
 
 template <typename P>
@@ -350,16 +371,22 @@ void host_init(spz_ctx* c, std::vector<float>& img) {
       const Lay& L = c->net[ni].L[l];
       const double k = (double)(float)(1.0 / std::sqrt((double)L.in_f));
       const uint32_t tw = (uint32_t)(ni * 16 + l * 2), tb = tw + 1;
-      for (int o = 0; o < L.out_f; ++o)
-        for (int i = 0; i < L.in_f; ++i) {
-          const uint64_t e = (uint64_t)o * L.in_f + i;
-          const double u = (double)(philox_word(c->seed, e, 0, P_INIT, tw) >> 8) * 0x1p-24;
-          img[L.w + (int64_t)o * L.in_p + pcol(c, ni, l, i)] = (float)((2.0 * u - 1.0) * k);
+      // four values to a Philox block
+      auto fill = [&](int64_t n, uint32_t tensor, auto&& at) {
+        for (int64_t e = 0; e < n; e += 4) {
+          const U4 w = philox(U4{(uint32_t)(e >> 2), 0u, P_INIT, tensor}, (uint32_t)c->seed, (uint32_t)(c->seed >> 32));
+          const uint32_t v[4] = {w.x, w.y, w.z, w.w};
+          for (int64_t i = e; i < std::min(e + 4, n); ++i) {
+            const double u = (double)(v[i - e] >> 8) * 0x1p-24;
+            img[at(i)] = (float)((2.0 * u - 1.0) * k);
+          }
         }
-      for (int o = 0; o < L.out_f; ++o) {
-        const double u = (double)(philox_word(c->seed, (uint64_t)o, 0, P_INIT, tb) >> 8) * 0x1p-24;
-        img[L.b + o] = (float)((2.0 * u - 1.0) * k);
-      }
+      };
+      fill((int64_t)L.in_f * L.out_f, tw, [&](int64_t e) {
+        const int64_t o = e / L.in_f;
+        return L.w + o * L.in_p + pcol(c, ni, l, (int)(e - o * L.in_f));
+      });
+      fill(L.out_f, tb, [&](int64_t e) { return L.b + e; });
     }
   }
   img[c->la] = c->td3 ? 0.0f : (float)std::log((double)c->hp.alpha_init);
@@ -1729,6 +1756,11 @@ int setup_layers(spz_ctx* c) {
   return SPZ_OK;
 }
 
+constexpr size_t PIN_BYTES = (size_t)1 << 20;
+// Observations of up to this size reach the sampler-action kernel through pinned memory;
+// above it the copy engine's rate outweighs its latency.
+constexpr size_t PIN_OBS_BYTES = (size_t)256 << 10;
+
 int setup(spz_ctx* c) {
   const size_t e = es(c);
   const int64_t Bp = c->Bp;
@@ -1749,6 +1781,7 @@ int setup(spz_ctx* c) {
   CK(dalloc_t(c, &c->V, ab));
   CK(dalloc_t(c, &c->T, ab));
   CK(dalloc_t(c, &c->d_step, 8));
+  CK(hipHostMalloc((void**)&c->pin, PIN_BYTES, hipHostMallocDefault));
   CK(dalloc_t(c, &c->rec, (size_t)c->rec_cap * SPZ_REC_WIDTH * 4));
   // batch
   const size_t xb = (size_t)Bp * c->Kc * e;
@@ -1816,6 +1849,7 @@ void release(spz_ctx* c) {
   if (c->ev_commit) (void)hipEventDestroy(c->ev_commit);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->stage) (void)hipFree(c->stage);
+  if (c->pin) (void)hipHostFree(c->pin);
   for (hipEvent_t e : c->pool) (void)hipEventDestroy(e);
   for (auto& pe : c->pevs) {
     (void)hipEventDestroy(pe.a);
@@ -2118,15 +2152,33 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
   for (int64_t r0 = 0; r0 < n && rc == SPZ_OK; r0 += chunk) {
     const int m = (int)std::min(chunk, n - r0);
     const int rows = (m + 255) / 256 * 256;
-    hipError_t e = hipMemcpy(c->stage, obs + r0 * c->O, (size_t)m * c->O * 4, hipMemcpyHostToDevice);
-    if (c->rows_on) {
-      if (e == hipSuccess) e = row_act(c, c->stage, m, r0, stochastic != 0, counter, c->th, s);
+    const size_t in_bytes = (size_t)m * c->O * 4, out_bytes = (size_t)m * c->A * 4;
+    float* act_dev = c->th;
+    const float* obs_dev = c->stage;
+    const bool pin_in = in_bytes <= PIN_OBS_BYTES, pin_out = out_bytes <= PIN_BYTES - PIN_OBS_BYTES;
+    if (pin_out) act_dev = reinterpret_cast<float*>(c->pin + PIN_OBS_BYTES);
+    hipError_t e = hipSuccess;
+    if (pin_in) {
+      std::memcpy(c->pin, obs + r0 * c->O, in_bytes);
+      obs_dev = reinterpret_cast<const float*>(c->pin);
+    } else {
+      e = hipMemcpy(c->stage, obs + r0 * c->O, in_bytes, hipMemcpyHostToDevice);
+    }
+    // The actions of this chunk, once the launches that make them are enqueued.
+    auto finish = [&] {
       if (e == hipSuccess) e = hipStreamSynchronize(s);
-      if (e == hipSuccess) e = hipMemcpy(act + r0 * c->A, c->th, (size_t)m * c->A * 4, hipMemcpyDeviceToHost);
+      if (e == hipSuccess) {
+        if (pin_out) std::memcpy(act + r0 * c->A, act_dev, out_bytes);
+        else e = hipMemcpy(act + r0 * c->A, act_dev, out_bytes, hipMemcpyDeviceToHost);
+      }
       if (e != hipSuccess) rc = set_err(c, SPZ_EHIP, std::string("spz_act: ") + hipGetErrorString(e));
+    };
+    if (c->rows_on) {
+      if (e == hipSuccess) e = row_act(c, obs_dev, m, r0, stochastic != 0, counter, act_dev, s);
+      finish();
       continue;
     }
-    ObsArgs oa{c->stage, m, rows, c->O, c->Ka, c->xsp, c->Kc};
+    ObsArgs oa{obs_dev, m, rows, c->O, c->Ka, c->xsp, c->Kc};
     if (e == hipSuccess) e = launch_obs_operand(c->bf16, oa, s);
     c->B = m;
     c->Bp = rows;
@@ -2135,11 +2187,9 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
     c->B = saveB;
     c->Bp = saveBp;
     ActHeadArgs ha{c->z, pa, c->A, m, r0, c->td3 ? 0 : 1, stochastic ? 1 : 0, c->seed, counter,
-                   c->hp.log_std_min, c->hp.log_std_max, c->th};
+                   c->hp.log_std_min, c->hp.log_std_max, act_dev};
     if (e == hipSuccess) e = launch_act_head(ha, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e == hipSuccess) e = hipMemcpy(act + r0 * c->A, c->th, (size_t)m * c->A * 4, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) rc = set_err(c, SPZ_EHIP, std::string("spz_act: ") + hipGetErrorString(e));
+    finish();
   }
   return rc;
 }
@@ -2476,14 +2526,31 @@ int spz_read_params(spz_ctx* c, int32_t which, float* out, int64_t n_floats) {
     return SPZ_OK;
   }
   const Net& n = c->net[ni];
-  std::vector<float> img((size_t)(n.end - n.off));
-  CK(hipMemcpy(img.data(), arena + n.off, img.size() * 4, hipMemcpyDeviceToHost));
+  FlatArgs f{};
+  f.arena = arena;
+  f.layers = (int)n.L.size();
   int64_t o = 0;
-  for (int l = 0; l < (int)n.L.size(); ++l) {
+  for (int l = 0; l < f.layers; ++l) {
     const Lay& L = n.L[l];
-    for (int r = 0; r < L.out_f; ++r)
-      for (int i = 0; i < L.in_f; ++i) out[o++] = img[L.w - n.off + (int64_t)r * L.in_p + pcol(c, ni, l, i)];
-    for (int r = 0; r < L.out_f; ++r) out[o++] = img[L.b - n.off + r];
+    const bool critic_in = ni != 0 && l == 0;
+    f.l[l] = FlatLayer{o, L.w, L.b, L.in_f, L.out_f, L.in_p, critic_in ? c->O : L.in_f, critic_in ? c->Ka - c->O : 0};
+    o += (int64_t)L.in_f * L.out_f + L.out_f;
+  }
+  // The device writes the flat layout into pinned memory, in two halves: one is filled while
+  // the other is copied out.
+  const int64_t half = (int64_t)(PIN_BYTES / 8);   // floats
+  auto fill = [&](int64_t first, int64_t chunk) {
+    f.first = first;
+    f.n = std::min(half, cnt - first);
+    f.out = reinterpret_cast<float*>(c->pin) + (chunk & 1) * half;
+    return f.n > 0 ? launch_flatten(f, c->sc) : hipSuccess;
+  };
+  CK(fill(0, 0));
+  for (int64_t first = 0, chunk = 0; first < cnt; first += half, ++chunk) {
+    CK(hipStreamSynchronize(c->sc));
+    CK(fill(first + half, chunk + 1));
+    std::memcpy(out + first, reinterpret_cast<const float*>(c->pin) + (chunk & 1) * half,
+                (size_t)std::min(half, cnt - first) * 4);
   }
   return SPZ_OK;
 }
@@ -2530,11 +2597,11 @@ int spz_read_losses(spz_ctx* c, float* out, int64_t first_step, int32_t n) {
   CK(hipSetDevice(c->hp.device));
   int rc = ctx_sync(c);
   if (rc) return rc;
-  for (int i = 0; i < n; ++i) {
-    const int64_t slot = (first_step - 1 + i) % c->rec_cap;
-    CK(hipMemcpy(out + (int64_t)i * SPZ_REC_WIDTH, c->rec + slot * SPZ_REC_WIDTH, SPZ_REC_WIDTH * 4,
-                 hipMemcpyDeviceToHost));
-  }
+  // at most two runs of consecutive records (the ring wraps)
+  const int64_t slot = (first_step - 1) % c->rec_cap, run = std::min<int64_t>(n, c->rec_cap - slot);
+  CK(hipMemcpy(out, c->rec + slot * SPZ_REC_WIDTH, (size_t)run * SPZ_REC_WIDTH * 4, hipMemcpyDeviceToHost));
+  if (run < n)
+    CK(hipMemcpy(out + run * SPZ_REC_WIDTH, c->rec, (size_t)(n - run) * SPZ_REC_WIDTH * 4, hipMemcpyDeviceToHost));
   return SPZ_OK;
 }
 

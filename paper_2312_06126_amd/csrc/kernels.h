@@ -267,6 +267,15 @@ hipError_t launch_adam(const AdamArgs& a, hipStream_t s);
 hipError_t launch_finish(const FinishArgs& f, hipStream_t s);
 hipError_t launch_to_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
 
+// A network in the flat layout of the ABI (per layer W [out, in], then b [out]) from its arena:
+// flat elements [first, first + n) go to out[0 .. n). Layer l's W starts at flat element f0 and
+// arena element w with row stride ld; its flat columns from `gap` on are shifted by `shift`
+// (the action block of a critic's first layer).
+struct FlatLayer { int64_t f0, w, b; int32_t in, out, ld, gap, shift; };
+constexpr int MAX_FLAT_LAYERS = 8;
+struct FlatArgs { const float* arena; float* out; int64_t first, n; int layers; FlatLayer l[MAX_FLAT_LAYERS]; };
+hipError_t launch_flatten(const FlatArgs& a, hipStream_t s);
+
 // Transposed weight images (operand type: bfloat16 or float32): job j writes
 // dst[dst_off + c * ldd + r] = src[src_off + r * lds + c]
 // for r < rows, c < cols (the [cols, rows] transpose of a [rows, cols] matrix); the

@@ -700,6 +700,25 @@ __global__ void __launch_bounds__(256) k_to_bf16(const float* __restrict__ src, 
   if (i < n) dst[i] = f2bf(src[i]);
 }
 
+__global__ void __launch_bounds__(256) k_flatten(FlatArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const int64_t f = a.first + i;
+  int k = 0;
+  while (k + 1 < a.layers && f >= a.l[k + 1].f0) ++k;
+  const FlatLayer L = a.l[k];
+  const int64_t e = f - L.f0, wn = (int64_t)L.in * L.out;
+  int64_t src;
+  if (e >= wn) {
+    src = L.b + (e - wn);
+  } else {
+    const int64_t r = e / L.in;
+    const int c = (int)(e - r * L.in);
+    src = L.w + r * L.ld + c + (c >= L.gap ? L.shift : 0);
+  }
+  a.out[i] = a.arena[src];
+}
+
 // One 64 x 64 tile of one transpose job per workgroup, through an LDS tile: reads of
 // 64 consecutive columns per row and writes of 64 consecutive rows per column.
 template <typename T>
@@ -866,6 +885,13 @@ hipError_t launch_finish(const FinishArgs& f, hipStream_t s) {
 }
 hipError_t launch_to_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s) {
   k_to_bf16<<<blocks(n, 256), 256, 0, s>>>(src, dst, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_flatten(const FlatArgs& a, hipStream_t s) {
+  if (a.layers < 1 || a.layers > MAX_FLAT_LAYERS || a.n < 0) return hipErrorInvalidValue;
+  if (!a.n) return hipSuccess;
+  k_flatten<<<blocks(a.n, 256), 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
