@@ -1222,11 +1222,14 @@ std::vector<RowWLayer> row_wlayers(const spz_ctx* c, int part) {
   return v;
 }
 
-// Slices the batch of a launch's weight gradients is split into: enough waves for the chip
-// and at least ROW_MIN_GROUPS row groups each.
-constexpr int ROW_TARGET_WAVES = 1024, ROW_MIN_GROUPS = 4;
+// Slices the batch of a launch's weight gradients is split into: a wave for each SIMD (1024),
+// two where a slice keeps 128 row groups (400-300 fp32, 32768 rows: 148 and 132 us; 2 x 256
+// fp32, 8192 rows, 64 and 32 groups: 33 and 36 us, as the slices have to be added up), and at
+// least ROW_MIN_GROUPS row groups each.
+constexpr int ROW_SIMDS = 1024, ROW_LONG_GROUPS = 128, ROW_MIN_GROUPS = 4;
 int row_slices(int tiles, int groups) {
-  return std::max(1, std::min(ROW_TARGET_WAVES / std::max(tiles, 1), groups / ROW_MIN_GROUPS));
+  const int one = std::max(ROW_SIMDS / tiles, 1), two = std::max(2 * ROW_SIMDS / tiles, 1);
+  return std::max(1, std::min(groups / two >= ROW_LONG_GROUPS ? two : one, groups / ROW_MIN_GROUPS));
 }
 int row_tiles(const spz_ctx* c, bool crit, bool act) {
   int t = 0;

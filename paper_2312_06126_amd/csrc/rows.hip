@@ -47,6 +47,51 @@ __device__ inline void mma(f32x16& acc, const u32x4& a, const u32x4& b) {
   }
 }
 
+// Eight float32 values of a lane (two steps' fragments) as a sum of three bfloat16 each: the
+// rounded value, the rounded rest and the rest of that, 24 bits and exact (the last rest has
+// at most 8 significant bits).
+struct Split { u32x4 p[3]; };
+__device__ inline Split split(const u32x4& lo, const u32x4& hi) {
+  Split s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 v = __builtin_bit_cast(f32x4, i < 2 ? lo : hi);
+    float a = v[2 * (i & 1)], b = v[2 * (i & 1) + 1];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const uint32_t w = pack_bf16x2(a, b);
+      s.p[t][i] = w;
+      if (t < 2) {
+        a -= __builtin_bit_cast(float, w << 16);
+        b -= __builtin_bit_cast(float, w & 0xFFFF0000u);
+      }
+    }
+  }
+  return s;
+}
+
+// acc += A B^T over two float32 steps (16 deep) on the bfloat16 matrix instructions: the six
+// products of at most 2^-18 of the largest and above, smallest first (the three left out are
+// below 2^-25 of it). 6 x 32 clocks where the float32 instructions take 8 x 64. Infinite
+// values give NaN (the rest of an infinity is one): the caller checks. For weight gradients
+// only: their distance from 64 bits does not grow (five networks, three seeds, per tensor: 0.7
+// to 1.0 of the float32 instructions'), while input gradients on split operands, 3 - 4% faster
+// a step, put the first layer's bias gradient up to 1.6 times further off.
+__device__ inline void mma_split(f32x16& acc, const Split& a, const Split& b) {
+  constexpr int A[6] = {2, 0, 1, 1, 0, 0}, B[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[A[i]]),
+                                                  __builtin_bit_cast(bf16x8, b.p[B[i]]), acc, 0, 0, 0);
+}
+
+__device__ inline bool has_nan(const f32x16& a) {
+  bool n = false;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) n |= a[q] != a[q];
+  return n;
+}
+
 __device__ inline void zero(f32x16& a) {
 #pragma unroll
   for (int q = 0; q < 16; ++q) a[q] = 0.0f;
@@ -257,11 +302,11 @@ __device__ inline void product(const RowArgs& g, const RowOp& o, const Lds& L, i
     }
   }
 #pragma unroll
-  for (int i = 0; i < PD; ++i) load(i, s0 + i);
-#pragma unroll
   for (int t = 1; t < TM; ++t)
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[t][j] = acc[0][j];
+#pragma unroll
+  for (int i = 0; i < PD; ++i) load(i, s0 + i);
   int s = s0;
   for (; s + PD < s1; s += PD) {
 #pragma unroll
@@ -625,8 +670,9 @@ __device__ inline void head_backward(const RowArgs& g, const RowOp& o, const Lds
   for (int e = tid; e < BM * rest; e += ROW_THREADS) H[e / rest * g.ldh + used + e % rest] = from_f<T>(0.0f);
 }
 
-// 32-row tiles: 128 registers, two workgroups per CU where their LDS allows it; 64-row tiles
-// take the LDS of a CU.
+// 32-row tiles: 128 registers, two workgroups per CU where their LDS allows it (where it does
+// not, 155 registers are slower: 400-300 fp32 1067 against 1028 us); 64-row tiles take the LDS
+// of a CU.
 template <typename T, int TM>
 __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs args) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -708,6 +754,11 @@ __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs a
 // One wave takes 2 x 2 blocks of a product over one slice of the batch, fragments straight
 // from memory into registers: no LDS, no barriers. The four waves of a workgroup and its
 // neighbours on the same XCD take neighbouring tiles of the same slice, which share fragments.
+// float32 runs on split operands: 400-300 (TD3) at 32768 rows 218 -> 148 us for the critics'
+// and 146 -> 101 us for the actor's and critics' launch share against the float32 instructions
+// (then 132 and 86 us with twice the slices), 2 x 256 at 8192 rows 43 -> 33 us. bf16 is bound by
+// L2: 46 us for 550 MB at 2 x 256 (376 inputs), 16384 rows. (4 x 2 blocks a wave, 96 instead of
+// 128 bytes a block and row, is slower in both: the registers leave too little in flight.)
 template <typename T>
 __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
   const int wgs = (W.tasks + 3) / 4;
@@ -730,15 +781,19 @@ __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
   const int local = task - J.task0, slice = local / tiles, tl = local - slice * tiles;
   const int m0 = tl / tn * 2, n0 = (tl - tl / tn * tn) * 2;
   const bool m2 = m0 + 1 < J.mblk, n2 = n0 + 1 < J.nblk;
-  const int g0 = (int)((int64_t)W.groups * slice / J.slices), g1 = (int)((int64_t)W.groups * (slice + 1) / J.slices);
+  const int pairs = W.groups / 2;   // (a multiple of 32 rows)
+  const int g0 = 2 * (int)((int64_t)pairs * slice / J.slices), g1 = 2 * (int)((int64_t)pairs * (slice + 1) / J.slices);
   const u32x4* a = static_cast<const u32x4*>(J.a) + (int64_t)m0 * 64 + lane;
   const u32x4* b = static_cast<const u32x4*>(J.b) + (int64_t)n0 * 64 + lane;
   const int64_t as = (int64_t)J.mblk * 64, bs = (int64_t)J.bcb * 64;
   const int am = m2 ? 64 : 0, bn = n2 ? 64 : 0;
   f32x16 acc[2][2];
+  auto clear = [&] {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) zero(acc[i >> 1][i & 1]);
-  constexpr int PD = sizeof(T) == 2 ? 4 : 2;
+    for (int i = 0; i < 4; ++i) zero(acc[i >> 1][i & 1]);
+  };
+  clear();
+  constexpr int PD = 4;
   u32x4 f0[PD][4], f1[PD][4];
   auto load = [&](u32x4 (&f)[PD][4], int gr) {
 #pragma unroll
@@ -750,7 +805,17 @@ __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
       f[i][3] = b[q * bs + bn];
     }
   };
-  auto multiply = [&](const u32x4 (&f)[PD][4], int gr) {
+  auto run = [&](auto&& multiply) {
+    if (g0 >= g1) return;
+    load(f0, g0);
+    for (int gr = g0; gr < g1; gr += 2 * PD) {
+      if (gr + PD < g1) load(f1, gr + PD);
+      multiply(f0, gr);
+      if (gr + 2 * PD < g1) load(f0, gr + 2 * PD);
+      if (gr + PD < g1) multiply(f1, gr + PD);
+    }
+  };
+  auto exact = [&](const u32x4 (&f)[PD][4], int gr) {
 #pragma unroll
     for (int i = 0; i < PD; ++i) {
       if (gr + i >= g1) break;
@@ -758,13 +823,25 @@ __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
       for (int x = 0; x < 4; ++x) mma<T>(acc[x >> 1][x & 1], f[i][x >> 1], f[i][2 + (x & 1)]);
     }
   };
-  if (g0 < g1) {
-    load(f0, g0);
-    for (int gr = g0; gr < g1; gr += 2 * PD) {
-      if (gr + PD < g1) load(f1, gr + PD);
-      multiply(f0, gr);
-      if (gr + 2 * PD < g1) load(f0, gr + 2 * PD);
-      if (gr + PD < g1) multiply(f1, gr + PD);
+  if constexpr (sizeof(T) == 2) {
+    run(exact);
+  } else {
+    // two row groups at a time on split operands (a slice has an even number of them)
+    run([&](const u32x4 (&f)[PD][4], int gr) {
+#pragma unroll
+      for (int i = 0; i < PD; i += 2) {
+        if (gr + i >= g1) break;
+        const Split a0 = split(f[i][0], f[i + 1][0]), a1 = split(f[i][1], f[i + 1][1]);
+        const Split b0 = split(f[i][2], f[i + 1][2]), b1 = split(f[i][3], f[i + 1][3]);
+        mma_split(acc[0][0], a0, b0);
+        mma_split(acc[0][1], a0, b1);
+        mma_split(acc[1][0], a1, b0);
+        mma_split(acc[1][1], a1, b1);
+      }
+    });
+    if (__any(has_nan(acc[0][0]) || has_nan(acc[0][1]) || has_nan(acc[1][0]) || has_nan(acc[1][1]))) {
+      clear();   // infinities or NaN: again in float32
+      run(exact);
     }
   }
 #pragma unroll
@@ -806,7 +883,7 @@ __device__ inline void store_packed(T* f, T* t, const RowPBlk& B, int m0, int n,
 template <typename T>
 __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   __shared__ float bc[4];
-  __shared__ float4 sh[256];
+  __shared__ double sh[1024];
   const AdamArgs& a = p.a;
   const RowPBlk B = p.blk[p.first + blockIdx.x];
   T* PF = static_cast<T*>(p.PF);
@@ -871,22 +948,22 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   }
   if (B.kind == 1) {
     // 16 columns as 4 pieces of 4, each summed by 64 threads over every 64th slice, then
-    // the thread sums in order.
+    // the thread sums in order; in double precision, as there may be thousands of slices.
     const int piece = tid & 3, grp = tid >> 2;
     const float* src = B.part + 4 * piece;
-    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int z = grp; z < p.vslices; z += 64) {
       const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)z * B.ld);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+      s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
     }
-    sh[tid] = s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sh[grp * 16 + 4 * piece + e] = s[e];
     __syncthreads();
     if (tid >= 16) return;
-    const float* f = reinterpret_cast<const float*>(sh);
-    float g = 0.0f;
-    for (int q = 0; q < 64; ++q) g += f[q * 16 + tid];
-    const float x = element(B.off + tid, g, t);
+    double g = 0.0;
+    for (int q = 0; q < 64; ++q) g += sh[q * 16 + tid];
+    const float x = element(B.off + tid, (float)g, t);
     if (B.fwd >= 0) {
       PF[B.fwd + tid] = from_f<T>(x);
       if (polyak) TF[B.fwd + tid] = from_f<T>(t);
@@ -894,15 +971,11 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     return;
   }
   if (B.kind == 2) {
-    float* f = reinterpret_cast<float*>(sh);
-    float s = 0.0f;
+    double s = 0.0;
     for (int z = tid; z < p.vslices * ROW_WAVES; z += 256) s += B.part[z];
-    f[tid] = s;
-    __syncthreads();
+    s = block_sum<256>(s, sh);
     if (tid != 0) return;
-    float g = 0.0f;
-    for (int q = 0; q < 256; ++q) g += f[q];
-    element(B.off, g, t);
+    element(B.off, (float)s, t);
     return;
   }
   __syncthreads();
