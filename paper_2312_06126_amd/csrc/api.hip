@@ -982,7 +982,7 @@ size_t row_layout(const spz_ctx* c, int tm, int nets, size_t scratch, RowArgs& g
   g.oZ = (int)off;   // actor output [bm, pa], or the two action gradients [bm, Ap]
   off += align16z((size_t)bm * std::max(g.zp, (c->td3 ? 1 : 2) * g.dp) * 4);
   g.oV = (int)off;
-  off += (size_t)6 * bm * 4;
+  off += (size_t)7 * bm * 4;
   g.oM = (int)off;   // mask bits: actor layers, then each layer of both critics
   for (int l = 0; l < nh; ++l) off += (size_t)3 * bm * pad32(c->hidden[l]) / 8;
   g.oS = (int)off;
@@ -1157,11 +1157,11 @@ struct RowBuilder {
     if (grads) grad_outputs(o, ni, n, l - 1);
     product(o);
   }
-  void load(bool xsa, bool pack) {
+  void load(int what) {
     RowOp o = op(ROW_LOAD);
-    o.flags = xsa;
+    o.flags = what;
     v.push_back(o);
-    if (!pack) return;
+    if (what != ROW_LOAD_SA) return;
     o = op(ROW_PACK);
     o.nblk = c->Kc / 32;
     o.pack[0] = c->xpk;
@@ -1173,17 +1173,17 @@ struct RowBuilder {
     v.push_back(o);
   }
   void critic_part() {
-    load(false, false);
+    load(ROW_LOAD_NEXT);
     forward(0, 1, c->td3, false, false);
     head(false);
     critics(true, false, false, 2, ROW_DOT_TARGET);
-    load(true, true);
+    load(ROW_LOAD_SA);
     critics(false, true, true, 2, ROW_DOT_CLOSS);
     for (int ni = 1; ni <= 2; ni += nets) critic_back(ni, nets, true);
   }
   void actor_part() {
     const int n = c->td3 ? 1 : 2;
-    load(true, false);
+    load(ROW_LOAD_S);
     forward(0, 1, false, true, true);
     head(true);
     critics(false, true, false, n, ROW_DOT_ALOSS);
@@ -1381,7 +1381,9 @@ hipError_t row_step(spz_ctx* c, bool crit, bool act, hipStream_t s) {
   if (act) { g.op0[i] = P.n_crit; g.nops[i++] = P.n_act; }
   g.B = c->B;
   g.seed = c->seed; g.step = c->d_step;
-  g.xsa = c->xsa; g.xs2 = c->xs2; g.r = c->r; g.d = c->d; g.log_alpha = log_alpha_ptr(c);
+  g.ring = c->buf; g.row_bytes = c->row_bytes; g.size = (uint32_t)c->size;
+  g.off_a = c->off_a; g.off_s2 = c->off_s2; g.off_r = c->off_r; g.off_d = c->off_d;
+  g.xsa = c->xsa; g.xs2 = c->xs2; g.r = c->r; g.d = c->d; g.idx = c->idx; g.log_alpha = log_alpha_ptr(c);
   g.gamma = c->hp.gamma; g.lmin = c->hp.log_std_min; g.lmax = c->hp.log_std_max;
   g.noise = c->hp.policy_noise; g.clip = c->hp.noise_clip;
   g.y = c->y; g.q1 = c->q1; g.q2 = c->q2; g.qp1 = c->qp1; g.qp2 = c->qp2; g.logp = c->logp;
@@ -1506,8 +1508,7 @@ hipError_t adam(spz_ctx* c, bool critics, bool actor_step, bool actor, int step_
   return refresh_wt(c, s);
 }
 
-// The step after the gather on the row-tile path, all on s0 (the two halves of a snapshot
-// step share a launch).
+// The step on the row-tile path, all on s0 (the two halves of a snapshot step share a launch).
 hipError_t row_enqueue(spz_ctx* c, bool actor_step, bool sequential, hipStream_t s0) {
   const FinishArgs f = finish_args(c, row_tile_count(c->B, row_tm(c, c->B)) * ROW_WAVES, actor_step);
   double bytes = 0.0;
@@ -1536,24 +1537,23 @@ int enqueue_step(spz_ctx* c, hipStream_t s0) {
   } step_timing{c};
   c->pf_step = t % c->pf_stride == 0;
   const bool rows = c->rows_on;
-  const bool two = c->hp.n_streams == 2 && !sequential && !rows;
   c->last_rows = rows;
-  c->xs_act = two ? c->xsp : c->xsa;
-  // The row-tile path keeps the policy's actions in LDS: xsa holds the sampled ones.
-  GatherArgs g{c->buf, c->row_bytes, c->off_a, c->off_s2, c->off_r, c->off_d, c->O, c->A, c->Ka, c->Kc,
-               c->B, c->seed, (uint32_t)c->size, c->d_step, c->xsa, c->xs2, two ? c->xsp : nullptr, c->r, c->d,
-               c->idx, two || rows ? nullptr : c->abuf};
-  {
-    const double e = (double)es(c);
-    // s to xsa (and xsp on two streams), s' to xs2; a to xsa (and abuf on one stream)
-    const double copies = two ? 3.0 : 2.0, acopies = two || rows ? 1.0 : 2.0;
-    const double bytes = (double)c->B * ((2.0 * c->O + c->A) * e + 8.0 + (copies * c->O + acopies * c->A) * e + 12.0);
-    CK(timed(c, "gather", c->B, c->O, c->A, 0.0, bytes, s0, [&] { return launch_gather(c->bf16, g, s0); }));
-  }
-  if (rows) {
+  if (rows) {   // samples the batch itself
     CK(row_enqueue(c, actor_step, sequential, s0));
     c->h_step = t;
     return SPZ_OK;
+  }
+  const bool two = c->hp.n_streams == 2 && !sequential;
+  c->xs_act = two ? c->xsp : c->xsa;
+  GatherArgs g{c->buf, c->row_bytes, c->off_a, c->off_s2, c->off_r, c->off_d, c->O, c->A, c->Ka, c->Kc,
+               c->B, c->seed, (uint32_t)c->size, c->d_step, c->xsa, c->xs2, two ? c->xsp : nullptr, c->r, c->d,
+               c->idx, two ? nullptr : c->abuf};
+  {
+    const double e = (double)es(c);
+    // s to xsa (and xsp on two streams), s' to xs2; a to xsa (and abuf on one stream)
+    const double copies = two ? 3.0 : 2.0, acopies = two ? 1.0 : 2.0;
+    const double bytes = (double)c->B * ((2.0 * c->O + c->A) * e + 8.0 + (copies * c->O + acopies * c->A) * e + 12.0);
+    CK(timed(c, "gather", c->B, c->O, c->A, 0.0, bytes, s0, [&] { return launch_gather(c->bf16, g, s0); }));
   }
   hipStream_t sc = s0, sa = s0;
   if (two) {

@@ -6,7 +6,7 @@
 
 namespace spz {
 
-// Everything between the replay gather and the weight gradients is local to a batch row,
+// Everything from the replay sampling to the weight gradients is local to a batch row,
 // so a workgroup takes a tile of 32 (bf16: or 64) rows through a list of operations (RowOp): the
 // layers of the target action, the target and online critics, the losses and the backward
 // chains. Weights come from packed images, activations and output gradients leave as
@@ -37,6 +37,7 @@ enum RowOpKind : int32_t {
   ROW_HEAD_BWD,  // Z (action gradients) -> actor output gradient in H
   ROW_ACT        // sampler actions from Z
 };
+enum RowLoadWhat : int32_t { ROW_LOAD_NEXT, ROW_LOAD_SA, ROW_LOAD_S };
 enum RowDotThen : int32_t { ROW_DOT_ONLY, ROW_DOT_TARGET, ROW_DOT_CLOSS, ROW_DOT_ALOSS };
 
 // Operand of two nets where an operation covers both critics (nets = 2: waves 0-3 take net0,
@@ -67,8 +68,11 @@ struct RowArgs {
   int oX, ldx, oH, ldh, hnet, oZ, zp, dp, oV, oM, oS;
   int A, Ka, Ap, Kc, pa, O, sac;
   uint64_t seed; const int64_t* step;
-  const void *xsa, *xs2;
-  const float *r, *d, *log_alpha;
+  // replay ring, and the gathered batch in global memory (debug reads): [Bp, Kc] operands
+  // (s | a) and (s' | 0), rewards, ends and ring rows
+  const uint8_t* ring; int64_t row_bytes; int off_a, off_s2, off_r, off_d; uint32_t size;
+  void *xsa, *xs2; float *r, *d; int32_t* idx;
+  const float* log_alpha;
   float gamma, lmin, lmax, noise, clip;
   float *y, *q1, *q2, *qp1, *qp2, *logp, *th, *se, *lm, *da;
   double *cpart, *apart;   // [tiles, ROW_WAVES] loss partials

@@ -8,9 +8,9 @@
 // fp32 is bound by the matrix cores (2 x 256 at 8192 rows: 60% of their rate in k_rows, 400-300
 // at 32768 rows: 77%), bf16 by the weights' way through the vector L1 (64 bytes a clock) and by
 // the fixed time of an operation, 2 - 3 thousand clocks of loads, epilogue and barriers.
-// Measured, a step against the layer-by-layer path: 2 x 64 fp32 at 256 rows 260 -> 53 us; 2 x
-// 256 fp32 at 8192 rows 520 -> 237 us; 400-300 fp32 (TD3) at 32768 rows 1.89 -> 1.45 ms; 2 x
-// 256 bf16 (376 inputs) at 16384 rows 420 -> 198 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 68 us.
+// Measured, a step against the layer-by-layer path: 2 x 64 fp32 at 256 rows 260 -> 51 us; 2 x
+// 256 fp32 at 8192 rows 520 -> 225 us; 400-300 fp32 (TD3) at 32768 rows 1.89 -> 1.31 ms; 2 x
+// 256 bf16 (376 inputs) at 16384 rows 420 -> 188 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 64 us.
 #include "rows.h"
 
 #include <atomic>
@@ -186,7 +186,8 @@ struct Lds {
   template <typename T> __device__ inline T* x() const { return reinterpret_cast<T*>(base + g.oX); }
   template <typename T> __device__ inline T* h(int slot) const { return reinterpret_cast<T*>(base + g.oH) + slot * g.hnet; }
   __device__ inline float* z() const { return reinterpret_cast<float*>(base + g.oZ); }
-  // per-row values: 0, 1 q of the two nets, 2 y, 3, 4 dq of the two nets, 5 log pi
+  // per-row values: 0, 1 q of the two nets, 2 y, 3, 4 r and d, then dq of the two nets, 5 log pi,
+  // 6 ring rows
   __device__ inline float* v(int i) const { return reinterpret_cast<float*>(base + g.oV) + i * 32 * g.tm; }
   __device__ inline uint16_t* m() const { return reinterpret_cast<uint16_t*>(base + g.oM); }
   __device__ inline f32x4* s() const { return reinterpret_cast<f32x4*>(base + g.oS); }
@@ -446,16 +447,66 @@ __device__ inline void output_backward(const RowArgs& g, const RowOp& o, const L
   }
 }
 
+// The tile's rows of the replay ring, sampled by Philox as in the layer-by-layer path's gather.
+// A ring row's segments start on 16 bytes and are zero past their last element, and so are
+// the operand's columns past each segment. The critic part also writes the batch to global
+// memory, where only debug reads look at it. A launch of its own for this wrote the batch and
+// read it back; without it a step of 2 x 64 fp32 at 256 rows takes 51 us (54), 2 x 256 bf16
+// at 16384 rows of 3.2 KB 188 us (198: the rows' 43 MB are 9 us of memory time either way).
 template <typename T, int TM>
 __device__ inline void load_tile(const RowArgs& g, const RowOp& o, const Lds& L, int64_t tile, int tid) {
   constexpr int VEC = RowT<T>::VEC, BM = 32 * TM;
-  const T* src = static_cast<const T*>(o.flags ? g.xsa : g.xs2) + tile * BM * (int64_t)g.Kc;
+  int32_t* rows = reinterpret_cast<int32_t*>(L.v(6));   // ring row, -1 past the batch
+  if (o.flags != ROW_LOAD_SA) {   // the first load of a part
+    if (tid < BM) {
+      const int64_t b = tile * BM + tid;
+      int32_t row = -1;
+      if (b < g.B) {
+        row = (int32_t)mulhi32(philox_word(g.seed, (uint64_t)b, (uint32_t)(*g.step + 1), P_IDX, 0u), g.size);
+        if (o.flags == ROW_LOAD_NEXT) {
+          const uint8_t* src = g.ring + (uint32_t)row * g.row_bytes;
+          const float r = *reinterpret_cast<const float*>(src + g.off_r), d = *reinterpret_cast<const float*>(src + g.off_d);
+          L.v(3)[tid] = r;
+          L.v(4)[tid] = d;
+          g.r[b] = r;
+          g.d[b] = d;
+          g.idx[b] = row;
+        }
+      }
+      rows[tid] = row;
+    }
+    __syncthreads();
+  }
+  const bool next = o.flags == ROW_LOAD_NEXT, act = o.flags == ROW_LOAD_SA;
+  const int seg = next ? g.off_s2 : 0;
+  const int ns = (g.O + VEC - 1) / VEC, na = act ? (g.A + VEC - 1) / VEC : 0, nk = g.Ka / VEC, nv = g.Kc / VEC;
   T* X = L.x<T>();
-  const int nv = g.Kc / VEC;
-#pragma unroll 4
-  for (int v = tid; v < BM * nv; v += ROW_THREADS) {
-    const int r = v / nv, c = (v - r * nv) * VEC;
-    *reinterpret_cast<u32x4*>(X + r * g.ldx + c) = *reinterpret_cast<const u32x4*>(src + (int64_t)v * VEC);
+  T* copy = o.flags == ROW_LOAD_S ? nullptr : static_cast<T*>(next ? g.xs2 : g.xsa) + tile * BM * (int64_t)g.Kc;
+  // Four reads of random rows in flight a thread: one at a time, each pays the whole latency of the memory.
+  constexpr int D = 4;
+  for (int v0 = tid; v0 < BM * nv; v0 += D * ROW_THREADS) {
+    u32x4 x[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      const int v = v0 + i * ROW_THREADS, r = v < BM * nv ? v / nv : 0, c = v - r * nv;
+      const int32_t row = rows[r];   // an unsigned index; -1 is past the largest ring
+      const bool s = c < ns, a = c >= nk && c < nk + na;
+      // what is not there reads the ring's first bytes and is zero
+      const uint8_t* src = g.ring;
+      const bool on = v < BM * nv && row != -1 && (s || a);
+      if (on) src += (uint32_t)row * g.row_bytes + (s ? seg + c * 16 : g.off_a + (c - nk) * 16);
+      x[i] = *reinterpret_cast<const u32x4*>(src);
+      if (!on) x[i] = {0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      const int v = v0 + i * ROW_THREADS;
+      if (v < BM * nv) {
+        const int r = v / nv, c = v - r * nv;
+        if (copy && rows[r] != -1) *reinterpret_cast<u32x4*>(copy + (int64_t)v * VEC) = x[i];
+        *reinterpret_cast<u32x4*>(X + r * g.ldx + c * VEC) = x[i];
+      }
+    }
   }
 }
 
@@ -480,11 +531,6 @@ __device__ inline void output_dot(const RowArgs& g, const RowOp& o, const Lds& L
   const int l = tid % LPR, r = tid / LPR, K = o.nblk * 32;
   const int64_t b = tile * (32 * TM) + r;
   const bool live = b < g.B;
-  float rew = 0.0f, done = 0.0f;
-  if (o.flags == ROW_DOT_TARGET && live) {
-    rew = g.r[b];
-    done = g.d[b];
-  }
   float q[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -520,7 +566,7 @@ __device__ inline void output_dot(const RowArgs& g, const RowOp& o, const Lds& L
   if (o.flags == ROW_DOT_TARGET) {
     float m = min_keep_nan(q[0], q[1]);
     if (g.sac) m -= expf(*g.log_alpha) * L.v(5)[r];
-    const float y = live ? rew + g.gamma * (1.0f - done) * m : 0.0f;
+    const float y = live ? L.v(3)[r] + g.gamma * (1.0f - L.v(4)[r]) * m : 0.0f;   // r, d of the load
     if (first) L.v(2)[r] = y;
     if (first && live) g.y[b] = y;
     return;

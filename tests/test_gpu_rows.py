@@ -34,7 +34,7 @@ def test_row_path_teacher_forced(w):
     g.update(1)
     names = {s["name"] for s in g.profile_read()}
     g.close()
-    assert names == {"gather", "row_step", "row_wgrad", "row_adam"}, names
+    assert names == {"row_step", "row_wgrad", "row_adam"}, names
     bf16 = w.prec == "bf16"
     teacher_forced(w, 4000, steps_before=1, n_steps=2, tol_grad=1e-3 if bf16 else FP32_TOL,
                    tol_loss=BF16_LOSS_TOL if bf16 else FP32_TOL)
