@@ -318,3 +318,12 @@ def test_dgrad_device_row_count(env, bf16, M, N, K, bits, out_f32):
     dC = torch.zeros((M, N), dtype=ctype, device="cuda")
     assert f(int(bf16), M, N, K, dA.data_ptr(), K, dB.data_ptr(), N, dC.data_ptr(), N,
              dbits.data_ptr() if bits else None, M, int(out_f32), 128) == spz.SPZ_EINVAL
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("M,N,K", [(128, 64, 64), (128, 32, 128), (384, 64, 192), (256, 96, 384), (128, 160, 256),
+                                   (65536, 64, 128)])
+def test_small_tile_slice_depths(env, bf16, M, N, K):
+    """Tiles up to 64 x 64 take whole 256-byte slices of K where K divides into them and
+    32-element ones elsewhere; ragged column tiles and every tile size, both element types."""
+    run(env, bf16, 0, M, N, K, relu=1, use_bias=True, out_f32=1)
