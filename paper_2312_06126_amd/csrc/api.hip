@@ -1381,6 +1381,13 @@ hipError_t row_step(spz_ctx* c, bool crit, bool act, hipStream_t s) {
   if (act) { g.op0[i] = P.n_crit; g.nops[i++] = P.n_act; }
   g.B = c->B;
   g.seed = c->seed; g.step = c->d_step;
+  const void* images[3] = {c->TF, c->PF, c->PT};
+  for (int i = 0; i < 3; ++i) g.warm[i] = static_cast<const uint8_t*>(images[i]);
+  // Not where both halves of a SAC step share the launch: they read the same images at the same
+  // time, and the touches cost more than they save (2 x 256 fp32 at 8192 rows 226 -> 228 us, 2 x
+  // 64 at 256 rows 50.6 -> 51.5 us). One half alone, or TD3: TD3 2 x 256 bf16 at 4096 rows 65.0
+  // -> 61.5 us, 400-300 fp32 at 32768 rows 1305 -> 1277 us.
+  g.warm_lines = crit && act && !c->td3 ? 0 : (int)(c->n_arena * es(c) / 128);
   g.ring = c->buf; g.row_bytes = c->row_bytes; g.size = (uint32_t)c->size;
   g.off_a = c->off_a; g.off_s2 = c->off_s2; g.off_r = c->off_r; g.off_d = c->off_d;
   g.xsa = c->xsa; g.xs2 = c->xs2; g.r = c->r; g.d = c->d; g.idx = c->idx; g.log_alpha = log_alpha_ptr(c);

@@ -22,7 +22,7 @@ constexpr int ROW_THREADS = 512, ROW_WAVES = ROW_THREADS / 64;
 constexpr int ROW_MAX_BLOCKS = 4;   // 32-column blocks per wave of one operation
 
 enum RowOpKind : int32_t {
-  ROW_LOAD,      // batch operand tile -> X (flags 1: xsa, 0: xs2); pack[0]: packed image
+  ROW_LOAD,      // sampled rows of the replay ring -> X (flags: RowLoadWhat)
   ROW_OBS,       // sampler observations -> X
   ROW_HIDDEN,    // H = relu(A W^T + b); ReLU mask bits at `mask`; pack: packed image of H
   ROW_Z,         // Z = A W^T + b (actor output)
@@ -72,6 +72,7 @@ struct RowArgs {
   // (s | a) and (s' | 0), rewards, ends and ring rows
   const uint8_t* ring; int64_t row_bytes; int off_a, off_s2, off_r, off_d; uint32_t size;
   void *xsa, *xs2; float *r, *d; int32_t* idx;
+  const uint8_t* warm[3]; int warm_lines;   // packed images to bring into L2: 128-byte lines of each
   const float* log_alpha;
   float gamma, lmin, lmax, noise, clip;
   float *y, *q1, *q2, *qp1, *qp2, *logp, *th, *se, *lm, *da;

@@ -716,6 +716,25 @@ __device__ inline void head_backward(const RowArgs& g, const RowOp& o, const Lds
   for (int e = tid; e < BM * rest; e += ROW_THREADS) H[e / rest * g.ldh + used + e % rest] = from_f<T>(0.0f);
 }
 
+// Brings the operation list and the packed images into the L2 of the workgroup's XCD, which
+// starts a launch without them: each operation would wait for its record and then for its
+// weights from beyond L2. Workgroup b runs on XCD b % 8; those of an XCD share the lines, a word
+// of each a lane. The loads run beside the first operation's; t holds them until it is done.
+constexpr int WARM = 4;
+__device__ inline void warm_l2(const RowArgs& g, int part, int tid, uint32_t (&t)[WARM + 1]) {
+  const int n = max(1, (int)gridDim.x / 8), id = blockIdx.x / 8, lines = g.warm_lines;
+  const int bytes = g.nops[part] * (int)sizeof(RowOp);
+  t[WARM] = 0;
+  if (tid * 128 < bytes) t[WARM] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(g.ops + g.op0[part]) + tid * 128);
+#pragma unroll
+  for (int i = 0; i < WARM; ++i) {
+    const int v = (i * n + id) * ROW_THREADS + tid;
+    const int w = (v >= lines) + (v >= 2 * lines);
+    t[i] = 0;
+    if (id < n && v < 3 * lines) t[i] = *reinterpret_cast<const uint32_t*>(g.warm[w] + (int64_t)(v - w * lines) * 128);
+  }
+}
+
 // 32-row tiles: 128 registers, two workgroups per CU where their LDS allows it (where it does
 // not, 155 registers are slower: 400-300 fp32 1067 against 1028 us); 64-row tiles take the LDS
 // of a CU.
@@ -759,7 +778,17 @@ __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs a
         else if (o.split > 1 || o.from_h) __syncthreads();
         break;
       }
-      case ROW_LOAD: load_tile<T, TM>(g, o, L, tile, tid); break;
+      case ROW_LOAD: {
+        uint32_t t[WARM + 1];
+        const bool warm = g.warm_lines > 0 && o.flags != ROW_LOAD_SA;
+        if (warm) warm_l2(g, part, tid, t);
+        load_tile<T, TM>(g, o, L, tile, tid);
+        if (warm) {
+#pragma unroll
+          for (int i = 0; i <= WARM; ++i) asm volatile("" ::"v"(t[i]));
+        }
+        break;
+      }
       case ROW_OBS: {
         T* X = L.x<T>();
         for (int e = tid; e < BM * g.Ka; e += ROW_THREADS) {
