@@ -39,7 +39,9 @@ if ROOT not in sys.path:
 METRIC = "actor-critic update frames/sec (batch rows/s) at 1 MI355X; MFMA util %"
 PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}   # MI355X dense matrix peaks
 PEAK_HBM_GBS = 8000.0
-GEMMS = ("gemm_fwd", "gemm_dgrad", "gemm_wgrad")
+# Matrix-product kernels; row_step and row_wgrad are the two of the row-tile path (row_step
+# also samples the batch and runs the heads and losses).
+GEMMS = ("gemm_fwd", "gemm_dgrad", "gemm_wgrad", "row_step", "row_wgrad")
 SURVEY_STEPS = 10   # untimed steps with every kernel launch timed (per-kernel table)
 # In the timed region the dominant kernel's launches carry events in every
 # TIMED_STRIDE-th step only (each event pair costs the GPU a few microseconds).
@@ -177,7 +179,7 @@ def timed_rate(g, w, stream, steps: int, warmup: int):
                 steps=steps, warmup=warmup)
 
 
-def hbm_kernels(survey, names=("gather", "adam_polyak")):
+def hbm_kernels(survey, names=("gather", "adam_polyak", "row_adam")):
     """Achieved HBM rate of the memory-bound kernels of the step (algorithmic bytes per
     launch over the mean event-measured duration in the survey pass) against 8 TB/s."""
     out = {}

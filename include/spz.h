@@ -119,7 +119,9 @@ typedef struct spz_hparams {
   float policy_noise, noise_clip; /* TD3 target policy smoothing                   */
   int32_t policy_delay;           /* TD3: actor and targets every policy_delay steps */
   int32_t device;                 /* HIP device ordinal                            */
-  int32_t n_streams;              /* 2: actor and critic on concurrent streams; 1: one stream */
+  int32_t n_streams;              /* 2: actor and critic on concurrent streams; 1: one stream
+                                     (networks narrow enough for row tiles run both in one
+                                     launch either way)                               */
   int32_t ordering;               /* SPZ_ORDER_SNAPSHOT | SPZ_ORDER_SEQUENTIAL (below)     */
   int32_t actor_row_split;        /* SAC: 1 takes the actor loss's gradient through each
                                      critic only on the rows where that critic attains
@@ -127,7 +129,8 @@ typedef struct spz_hparams {
                                      there, Section 3.2.2's twin-critic minimum), with
                                      the same results as 0, which takes both critics
                                      over every row. Used where the ReLU masks are kept
-                                     as bits (bf16 with 128-multiple hidden widths).  */
+                                     as bits (bf16 with 128-multiple hidden widths) and the
+                                     layers run one by one.                           */
   int32_t graphs;                 /* 1: spz_update replays each step from a captured HIP
                                      graph (one per step kind: SAC has one, TD3 one with
                                      and one without the delayed actor update) instead of
@@ -237,7 +240,7 @@ int spz_act(spz_ctx* ctx, const float* obs, int64_t n, int32_t stochastic, uint3
  * and shared by every call on that GPU: calls that overlap on one GPU (other streams,
  * other threads, other contexts) race, so order them on one stream or synchronize
  * between them. The call writes every scratch byte it reads, so the previous call's
- * contents do not matter. n is limited by that array: at most the largest multiple
+ * contents do not matter. (Networks on the row-tile path keep these values on chip.) n is limited by that array: at most the largest multiple
  * of 256 rows with e * (pad32(obs_dim) + 2 * max_l pad32(hidden[l])) + 4 * pad32(out)
  * bytes per row (e = 2 for bf16 GEMM operands, 4 for fp32; out = 2*act_dim for SAC,
  * act_dim for TD3), plus alignment, within 64 MiB; larger n gives SPZ_EINVAL with

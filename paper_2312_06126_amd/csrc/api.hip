@@ -25,6 +25,9 @@
 //   s0: join -> finish (loss record, temperature gradient, step counter) -> Adam + Polyak
 // Sequential ordering (the published algorithms' order) runs everything on s0 and
 // moves the critics' Adam + Polyak between the critic part and the actor part.
+// Narrow networks take the row-tile path instead (rows.h; row_fits, row_batch), all on s0:
+// both parts up to the output gradients in one launch, which samples its rows itself, then
+// the weight gradients and the loss record, then reductions, Adam + Polyak and packed images.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
