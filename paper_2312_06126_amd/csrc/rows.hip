@@ -988,15 +988,18 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   const bool actor = B.net == 0;
   const bool polyak = actor ? a.polyak_actor : a.polyak_critic;
   const float lr = actor ? a.lr_a : a.lr_c;
-  auto element = [&](int64_t i, float g, float& t) {
+  // A parameter's state is read before its slices are summed: one memory latency, not two (2 x
+  // 64 fp32 7.7 -> 6.7 us, 2 x 256 bf16 13.0 -> 11.7, 200-120 fp32 19.8 -> 17.0 in two launches).
+  struct Old { float p, m, v, t; };
+  auto old = [&](int64_t i) { return Old{a.P[i], a.M[i], a.V[i], polyak ? a.T[i] : 0.0f}; };
+  auto element = [&](int64_t i, Old o, float g, float& t) {
     a.G[i] = g;
-    float m = a.M[i], v = a.V[i];
-    const float x = adam_element(a, a.P[i], m, v, g, lr, bc[actor ? 2 : 0], bc[actor ? 3 : 1]);
-    a.M[i] = m;
-    a.V[i] = v;
+    const float x = adam_element(a, o.p, o.m, o.v, g, lr, bc[actor ? 2 : 0], bc[actor ? 3 : 1]);
+    a.M[i] = o.m;
+    a.V[i] = o.v;
     a.P[i] = x;
     if (polyak) {
-      t = (1.0f - a.tau) * a.T[i] + a.tau * x;
+      t = (1.0f - a.tau) * o.t + a.tau * x;
       a.T[i] = t;
     }
     return x;
@@ -1006,6 +1009,9 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     const RowPJob J = p.j[B.job];
     const float4* src = reinterpret_cast<const float4*>(J.part) + (int64_t)B.blk * 256 + tid;
     const int64_t zs = J.zstride / 4;
+    Old o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = old(B.off + (int64_t)(m0 + j) * B.ld + n);
     float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll 8
     for (int z = 0; z < J.slices; ++z) {
@@ -1016,7 +1022,7 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     const float g[4] = {s.x, s.y, s.z, s.w};
     float v[4], u[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = element(B.off + (int64_t)(m0 + j) * B.ld + n, g[j], u[j]);
+    for (int j = 0; j < 4; ++j) v[j] = element(B.off + (int64_t)(m0 + j) * B.ld + n, o[j], g[j], u[j]);
     store_packed<T>(PF, PT, B, m0, n, v);
     if (polyak) store_packed<T>(TF, nullptr, B, m0, n, u);
     return;
@@ -1026,6 +1032,8 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     // the thread sums in order; in double precision, as there may be thousands of slices.
     const int piece = tid & 3, grp = tid >> 2;
     const float* src = B.part + 4 * piece;
+    Old o{};
+    if (tid < 16) o = old(B.off + tid);
     double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int z = grp; z < p.vslices; z += 64) {
@@ -1038,7 +1046,7 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     if (tid >= 16) return;
     double g = 0.0;
     for (int q = 0; q < 64; ++q) g += sh[q * 16 + tid];
-    const float x = element(B.off + tid, (float)g, t);
+    const float x = element(B.off + tid, o, (float)g, t);
     if (B.fwd >= 0) {
       PF[B.fwd + tid] = from_f<T>(x);
       if (polyak) TF[B.fwd + tid] = from_f<T>(t);
@@ -1050,7 +1058,7 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     for (int z = tid; z < p.vslices * ROW_WAVES; z += 256) s += B.part[z];
     s = block_sum<256>(s, sh);
     if (tid != 0) return;
-    element(B.off, (float)s, t);
+    element(B.off, old(B.off), (float)s, t);
     return;
   }
   __syncthreads();
