@@ -8,9 +8,9 @@
 // fp32 is bound by the matrix cores (2 x 256 at 8192 rows: 60% of their rate in k_rows, 400-300
 // at 32768 rows: 77%), bf16 by the weights' way through the vector L1 (64 bytes a clock) and by
 // the fixed time of an operation, 2 - 3 thousand clocks of loads, epilogue and barriers.
-// Measured, a step against the layer-by-layer path: 2 x 64 fp32 at 256 rows 260 -> 51 us; 2 x
-// 256 fp32 at 8192 rows 520 -> 225 us; 400-300 fp32 (TD3) at 32768 rows 1.89 -> 1.31 ms; 2 x
-// 256 bf16 (376 inputs) at 16384 rows 420 -> 188 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 64 us.
+// Measured, a step against the layer-by-layer path: 2 x 64 fp32 at 256 rows 260 -> 50 us; 2 x
+// 256 fp32 at 8192 rows 520 -> 225 us; 400-300 fp32 (TD3) at 32768 rows 1.89 -> 1.28 ms; 2 x
+// 256 bf16 (376 inputs) at 16384 rows 420 -> 188 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 60 us.
 #include "rows.h"
 
 #include <atomic>
