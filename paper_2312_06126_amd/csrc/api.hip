@@ -35,6 +35,7 @@
 #include <mutex>
 #include <new>
 
+#include "../../include/spz_testing.h"
 #include "rows.h"
 
 using namespace spz;
@@ -1244,6 +1245,26 @@ int row_tiles(const spz_ctx* c, bool crit, bool act) {
       }
   return t;
 }
+// Floats of the slices of one launch's weight gradients over `groups` row groups.
+int64_t row_wgrad_floats(const spz_ctx* c, bool crit, bool act, int groups) {
+  int64_t n = 0;
+  for (int part = 0; part < 2; ++part)
+    if (part ? act : crit)
+      for (const RowWLayer& w : row_wlayers(c, part)) {
+        const Lay& L = c->net[w.ni].L[w.l];
+        n += (int64_t)L.out_p * L.in_p;
+      }
+  return n * row_slices(row_tiles(c, crit, act), groups);
+}
+// The most any launch at up to `rows` rows (a multiple of 64) needs: of the critics, of the
+// actor or of both. None of the three bounds another: a launch of more products has fewer
+// slices, but may be the one whose slices are long enough for two waves a SIMD. Of one launch
+// the slices only grow with the batch.
+int64_t row_wgrad_cap(const spz_ctx* c, int rows) {
+  const int groups = rows / row_ks(c);
+  return std::max({row_wgrad_floats(c, true, false, groups), row_wgrad_floats(c, false, true, groups),
+                   row_wgrad_floats(c, true, true, groups)});
+}
 
 // Rebuilds the packed weight images from P and T.
 hipError_t refresh_packed(spz_ctx* c, hipStream_t s) {
@@ -1281,18 +1302,8 @@ int setup_rows(spz_ctx* c) {
       CK(dalloc_t(c, &c->bpart[ni][l], nt * (ni && l == nl - 1 ? ROW_WAVES : c->net[ni].L[l].out_p) * 4));
     if (ni) CK(dalloc_t(c, &c->wpart_out[ni], nt * c->net[ni].L[nl - 1].in_p * 4));
   }
-  // Weight-gradient slices: a step's launches use the workspace one after the other; slice
-  // counts grow with the batch and with fewer products in the launch.
-  const int groups = (int)(Bp / row_ks(c));
-  for (int part = 0; part < 2; ++part) {
-    const int slices = row_slices(row_tiles(c, part == 0, part == 1), groups);
-    int64_t n = 0;
-    for (const RowWLayer& w : row_wlayers(c, part)) {
-      const Lay& L = c->net[w.ni].L[w.l];
-      n += (int64_t)slices * L.out_p * L.in_p;
-    }
-    c->wg_cap += n;
-  }
+  // Weight-gradient slices: a step's launches use the workspace one after the other.
+  c->wg_cap = row_wgrad_cap(c, (int)Bp);
   CK(dalloc_t(c, &c->wg_part, (size_t)c->wg_cap * 4));
   // reduction + Adam work list
   std::vector<RowPBlk> blk;
@@ -2778,5 +2789,27 @@ int spz_profile_read(spz_ctx* c, spz_kernel_stat* out, int32_t max, int32_t* n_o
 }
 
 const char* spz_last_error(const spz_ctx* c) { return c ? c->err.c_str() : tl_err.c_str(); }
+
+// Test hook: no HIP call, no context.
+int spzt_row_workspace(int32_t td3, int32_t bf16, int32_t obs_dim, int32_t act_dim, const int32_t* hidden,
+                       int32_t n_hidden, int32_t created, int32_t batch, int64_t* cap, int64_t* need) {
+  if (obs_dim < 1 || act_dim < 1 || !hidden || n_hidden < 1 || n_hidden > 6 || batch < 1 || created < batch || !cap ||
+      !need)
+    return SPZ_EINVAL;
+  spz_ctx c;
+  c.O = obs_dim;
+  c.A = act_dim;
+  c.hidden.assign(hidden, hidden + n_hidden);
+  c.td3 = td3 != 0;
+  c.bf16 = bf16 != 0;
+  plan_layout(&c);
+  *cap = *need = 0;
+  if (!row_fits(&c)) return SPZ_OK;
+  *cap = row_wgrad_cap(&c, (created + 255) / 256 * 256);
+  for (int tm = 1; tm <= (c.bf16 ? 2 : 1); ++tm)
+    for (int what = 1; what <= 3; ++what)
+      *need = std::max(*need, row_wgrad_floats(&c, what & 1, what & 2, row_tile_count(batch, tm) * 32 * tm / row_ks(&c)));
+  return SPZ_OK;
+}
 
 }  // extern "C"

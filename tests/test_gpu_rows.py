@@ -3,6 +3,7 @@ layers it accepts (one critic at a time), heads of 1 and 32 actions, batches bel
 past its tiles, and the batch at which networks with the row split change paths."""
 import numpy as np
 import pytest
+import torch   # before the library: the first of the two to load chooses the HIP runtime
 
 import synth
 from synth.workloads import Workload
@@ -37,6 +38,25 @@ def test_row_path_teacher_forced(w):
     assert names == {"row_step", "row_wgrad", "row_adam"}, names
     bf16 = w.prec == "bf16"
     teacher_forced(w, 4000, steps_before=1, n_steps=2, tol_grad=1e-3 if bf16 else FP32_TOL,
+                   tol_loss=BF16_LOSS_TOL if bf16 else FP32_TOL)
+
+
+# Batches at which the joint launch of actor and critics needs a larger workspace of
+# weight-gradient slices than the launches of either added up.
+JOINT = [
+    Workload("sac_fp32_32k", "sac", 17, 6, (256, 256), 32768, 40000, "fp32", 0, target_entropy=-6.0),
+    Workload("sac_bf16_64k", "sac", 17, 6, (256, 256), 65536, 70000, "bf16", 0, target_entropy=-6.0),
+    Workload("td3_fp32_16k", "td3", 111, 8, (400, 300), 16384, 40000, "fp32", 0, learn_alpha=False, alpha_init=0.0),
+]
+
+
+@pytest.mark.parametrize("w", JOINT, ids=[w.name for w in JOINT])
+def test_joint_weight_gradients_teacher_forced(w):
+    """Steps that take the actor's and the critics' weight gradients in one launch, against
+    the oracle (bounds as for the other teacher-forced tests)."""
+    log("joint weight gradients %s" % w.name)
+    bf16 = w.prec == "bf16"
+    teacher_forced(w, 4000, steps_before=1, n_steps=1, tol_grad=1e-3 if bf16 else FP32_TOL,
                    tol_loss=BF16_LOSS_TOL if bf16 else FP32_TOL)
 
 
@@ -75,7 +95,6 @@ def test_set_batch_across_the_path_change_bit_exact(b):
 def test_layered_actions_from_any_alignment(prec, obs_dim):
     """The layer-by-layer action call (a layer past the row tiles) reads rows of four-column
     multiples on 16 bytes whole and others by the element: the same actions."""
-    torch = pytest.importorskip("torch")
     from paper_2312_06126_amd import Spz
     g = Spz(obs_dim, 3, (544,), 256, dict(algo="sac", gemm_prec=prec, capacity=256), 1)
     obs = np.random.default_rng(0).standard_normal((77, obs_dim)).astype(np.float32)
