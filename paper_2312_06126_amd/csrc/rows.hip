@@ -21,8 +21,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -111,17 +109,17 @@ __device__ inline uint32_t pk_min1(uint32_t x) {   // min(x, 1) of both halves
 }
 
 // ReLU of the accumulators, rounded to the operand type, and its mask: 16 bits, 1 where the
-// stored value is not zero. bf16: the pairs' low halves in bits 7 .. 0, high halves in 15 .. 8.
-// (bf16 drops a negative NaN, as the large-tile kernel's epilogue does; the hardware makes
-// positive ones.)
+// stored value is not zero (fp32: above zero). bf16: the pairs' low halves in bits 7 .. 0, high
+// halves in 15 .. 8. A NaN of either sign stays one, so that it reaches the loss record (the
+// matrix instructions make negative ones, so the ReLU is not taken on the rounded bits).
 template <typename T>
 __device__ inline uint32_t relu_block(const f32x16& acc, Block<T>& b) {
   uint32_t bits = 0;
   if constexpr (sizeof(T) == 2) {
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      const i16x2 v = __builtin_bit_cast(i16x2, pack_bf16x2(acc[2 * p], acc[2 * p + 1]));
-      b.w[p] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, (i16x2){0, 0}));
+      b.w[p] = pack_bf16x2(__builtin_elementwise_maximum(acc[2 * p], 0.0f),
+                           __builtin_elementwise_maximum(acc[2 * p + 1], 0.0f));
       bits = (bits << 1) | pk_min1(b.w[p]);
     }
     bits = __builtin_amdgcn_perm(0u, bits, 0x0C0C0200u);   // bytes 2, 0

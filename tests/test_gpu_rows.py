@@ -110,3 +110,29 @@ def test_layered_actions_from_any_alignment(prec, obs_dim):
     host = g.act(obs)
     g.close()
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], host)
+
+
+@pytest.mark.parametrize("negative", [False, True], ids=["pos", "neg"])
+@pytest.mark.parametrize("prec,hidden,batch", [
+    ("bf16", (64,), 300), ("bf16", (200, 120), 300), ("bf16", (256, 256), 2000), ("fp32", (200, 120), 300)])
+def test_nan_reaches_actions_and_loss_record(prec, hidden, batch, negative):
+    """A NaN of either sign, in an observation column or in a critic's first bias, makes the
+    actions that depend on it NaN and sets the step's non-finite flag."""
+    nan = np.uint32(0xFFC00000 if negative else 0x7FC00000).reshape(1).view(np.float32)[0]
+    w = RAGGED.replace(name="nan", hidden=hidden, batch=batch, prec=prec)
+    rows = [np.array(x) for x in synth.workload_rows(w, 0, 2000, 0)]
+    g = make_gpu(w)
+    g.buffer_push(*rows)
+    p = g.read_params("critic1")
+    p[(w.obs_dim + w.act_dim) * hidden[0] + 5] = nan
+    g.write_params("critic1", p)
+    g.update(1)
+    assert g.read_losses(1, 1)[0, 6] == 1.0
+    g.close()
+    rows[0][:, 3] = nan
+    g = make_gpu(w)
+    g.buffer_push(*rows)
+    assert np.isnan(g.act(rows[0][:33])).all()
+    g.update(1)
+    assert g.read_losses(1, 1)[0, 6] == 1.0
+    g.close()
