@@ -1822,6 +1822,7 @@ int setup(spz_ctx* c) {
   c->rows_ok = row_fits(c);
   c->layers_ok = !row_batch(c, 1);   // some batch size takes the layer-by-layer path
   c->rows_on = row_batch(c, c->B);
+  c->last_rows = c->rows_on;   // debug reads before the first step look at buffers that are there
   if (c->rows_ok) {
     const int rc = setup_rows(c);
     if (rc) return rc;

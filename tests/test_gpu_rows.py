@@ -136,3 +136,15 @@ def test_nan_reaches_actions_and_loss_record(prec, hidden, batch, negative):
     g.update(1)
     assert g.read_losses(1, 1)[0, 6] == 1.0
     g.close()
+
+
+@pytest.mark.parametrize("algo", ["sac", "td3"])
+@pytest.mark.parametrize("prec,hidden,n_streams,ordering", [
+    ("fp32", (64, 64), 1, "snapshot"), ("fp32", (64, 64), 2, "sequential"), ("bf16", (200, 120), 1, "snapshot"),
+    ("bf16", (256, 256), 1, "snapshot"), ("fp32", (544,), 1, "sequential")])
+def test_debug_reads_before_the_first_step_are_zero(algo, prec, hidden, n_streams, ordering):
+    base = RAGGED if algo == "sac" else RAGGED_TD3
+    g = make_gpu(base.replace(name="fresh", prec=prec, hidden=hidden, batch=300, ordering=ordering), n_streams=n_streams)
+    arrays = list(g.debug_batch()) + [g.debug_rows(k) for k in ("daction", "td_target", "q", "qpi")]
+    assert not any(np.any(a) for a in arrays) and not g.debug_indices().any()
+    g.close()
