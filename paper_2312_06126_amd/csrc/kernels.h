@@ -143,12 +143,17 @@ __device__ inline void adam_corrections(const AdamArgs& a, float* bc) {
   }
 }
 
-// One Adam step of a parameter (returned) and its moments.
+// One Adam step of a parameter (returned) and its moments; then Polyak of its target. The
+// fused operations are written out: which product of a sum the compiler rounds by itself would
+// otherwise depend on the code around it, and the kernels that share these would differ.
 __device__ inline float adam_element(const AdamArgs& a, float p, float& m, float& v, float g, float lr, float bc1,
                                      float bc2) {
-  m = a.b1 * m + (1.0f - a.b1) * g;
-  v = a.b2 * v + (1.0f - a.b2) * g * g;
+  m = fmaf(1.0f - a.b1, g, a.b1 * m);
+  v = fmaf((1.0f - a.b2) * g, g, a.b2 * v);
   return p - lr * (m / bc1) / (sqrtf(v / bc2) + a.eps);
+}
+__device__ inline float polyak_element(const AdamArgs& a, float t, float p) {
+  return fmaf(a.tau, p, (1.0f - a.tau) * t);
 }
 
 struct FinishArgs {

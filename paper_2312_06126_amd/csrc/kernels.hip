@@ -708,7 +708,7 @@ __global__ void __launch_bounds__(256) k_adam_polyak(AdamArgs a) {
   if (a.Pb) a.Pb[i] = f2bf(p);
   const bool pol = (in_critic && a.polyak_critic) || (in_actor && a.polyak_actor);
   if (pol) {
-    const float tb = (1.0f - a.tau) * a.T[i] + a.tau * p;
+    const float tb = polyak_element(a, a.T[i], p);
     a.T[i] = tb;
     if (a.Tb) a.Tb[i] = f2bf(tb);
   }

@@ -997,7 +997,7 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
     a.V[i] = o.v;
     a.P[i] = x;
     if (polyak) {
-      t = (1.0f - a.tau) * o.t + a.tau * x;
+      t = polyak_element(a, o.t, x);
       a.T[i] = t;
     }
     return x;

@@ -148,3 +148,33 @@ def test_debug_reads_before_the_first_step_are_zero(algo, prec, hidden, n_stream
     arrays = list(g.debug_batch()) + [g.debug_rows(k) for k in ("daction", "td_target", "q", "qpi")]
     assert not any(np.any(a) for a in arrays) and not g.debug_indices().any()
     g.close()
+
+
+@pytest.mark.parametrize("hidden", [(64, 40), (544, 40)], ids=["row_tiles", "layers"])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_adam_and_polyak_round_as_written(prec, hidden):
+    """Moments and targets of a step, bit for bit: one rounding of (1 - beta1) g + fl(beta1 m),
+    of fl((1 - beta2) g) g + fl(beta2 v) and of tau p + fl((1 - tau) target), on both paths.
+    The products are exact in the 64-bit significands used here; a sum that rounds twice there
+    would need its last 40 bits to hit the tie of the first rounding."""
+    w = RAGGED.replace(name="adam", hidden=hidden, batch=300, prec=prec)
+    g = make_gpu(w)
+    g.buffer_push(*synth.workload_rows(w, 0, 2000, 0))
+    g.update(3)
+    keys = [m + k for m in ("", "m_", "v_", "t") for k in ("actor", "critic1", "critic2") if m + k != "tactor"]
+    old = {k: g.read_params(k) for k in keys}
+    g.update(1)
+    hp = w.hparams()
+    one, f32, wide = np.float32(1), np.float32, np.longdouble
+    assert np.finfo(wide).nmant >= 63
+    b1, b2, tau = (f32(hp.get(k, d)) for k, d in (("beta1", 0.9), ("beta2", 0.999), ("tau", 0.005)))
+    for k in ("actor", "critic1", "critic2"):
+        grad = g.read_params("g_" + k)
+        m = (wide(one - b1) * grad.astype(wide) + (b1 * old["m_" + k]).astype(wide)).astype(f32)
+        v = (((one - b2) * grad).astype(wide) * grad.astype(wide) + (b2 * old["v_" + k]).astype(wide)).astype(f32)
+        assert np.array_equal(g.read_params("m_" + k), m), k
+        assert np.array_equal(g.read_params("v_" + k), v), k
+        if k != "actor":
+            t = (wide(tau) * g.read_params(k).astype(wide) + ((one - tau) * old["t" + k]).astype(wide)).astype(f32)
+            assert np.array_equal(g.read_params("t" + k), t), k
+    g.close()
