@@ -83,11 +83,17 @@ int spzt_bf16_round_check(uint64_t begin, uint64_t count, uint64_t* mismatches);
 /*
  * The row-tile path's weight-gradient workspace of a context created for `created` rows:
  * *cap floats allocated, *need the most that a launch of the critics, of the actor or of
- * both writes at `batch` (<= created) rows. Both 0 where the networks do not fit the path.
+ * both writes at `batch` (<= created) rows. Both 0 where that batch does not take the path.
  * Runs on the host alone.
  */
 int spzt_row_workspace(int32_t td3, int32_t bf16, int32_t obs_dim, int32_t act_dim, const int32_t* hidden,
                        int32_t n_hidden, int32_t created, int32_t batch, int64_t* cap, int64_t* need);
+/*
+ * The batches *lo .. *hi that networks of these sizes run on the row-tile path (0, 0: none).
+ * Runs on the host alone.
+ */
+int spzt_row_range(int32_t td3, int32_t bf16, int32_t sequential, int32_t n_streams, int32_t graphs, int32_t obs_dim,
+                   int32_t act_dim, const int32_t* hidden, int32_t n_hidden, int32_t* lo, int32_t* hi);
 
 #ifdef __cplusplus
 }

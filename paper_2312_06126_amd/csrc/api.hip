@@ -75,6 +75,8 @@ struct Lay {
   int64_t w, b;  // float offsets into an arena
 };
 
+struct RowRange { int lo, hi; };   // batches from lo to hi, both included
+
 struct Net {
   std::vector<Lay> L;
   int64_t off = 0, end = 0;
@@ -178,8 +180,9 @@ struct spz_ctx {
   // part's workspace and one launch at the end of the part reduces them all.
   struct RedQueue { float* base = nullptr; int64_t cap = 0, off = 0; double bytes = 0.0; ReduceJobs jobs{}; };
   RedQueue red[2];
-  // Row-tile path (rows.h): available when the networks fit it; whether the layer-by-layer
-  // path's buffers exist; which of the two the current batch takes; what the last step took.
+  // Row-tile path (rows.h): available when the networks fit it and some batch takes it; whether
+  // the layer-by-layer path's buffers exist; which of the two the current batch takes; what the
+  // last step took.
   struct RowPlan {   // one per tile height (index tm - 1)
     int nets = 2;          // nets per operation where both critics run
     RowOp* ops = nullptr;
@@ -189,6 +192,8 @@ struct spz_ctx {
   };
   RowPlan rplan[2];
   bool rows_ok = false, layers_ok = false, rows_on = false, last_rows = false;
+  RowRange row_range{};          // batches the row tiles take
+  int64_t rows_Bp = 0, layers_Bp = 0;   // (padded) rows either path's buffers hold
   void *xpk = nullptr, *dzh_pk = nullptr;
   std::vector<void*> hpk[3], dzpk[3];      // per net and hidden layer: packed activations and gradients
   std::vector<float*> bpart[3];            // per net and layer: bias-gradient partials
@@ -1023,24 +1028,70 @@ int row_nets(const spz_ctx* c, int tm) {
 }
 
 // Whether the networks fit the row-tile path. Policy heads of up to 64 outputs, as for the
-// head fused into the output product.
+// head fused into the output product; layers of up to 512 units, which is as wide as the path
+// has been laid out and tested for. (Not where it stops being the faster one: bfloat16 640-640,
+// 17 inputs, layer by layer over row tiles 2.1 at 8192 and 1.4 at 32768 rows, 1024-1024 1.15 and
+// 0.72; float32 640-640 0.90 at 256 and 1.42 at 16384 rows.)
 constexpr int ROW_MAX_WIDTH = 512;
 bool row_fits(const spz_ctx* c) {
   return c->net[0].L.back().out_p <= 64 && c->hmax <= ROW_MAX_WIDTH && row_nets(c, 1) > 0;
 }
 
-// SAC networks whose layers all have mask bits (bf16, 128-multiple widths) keep the
-// layer-by-layer path, with its row split and one timing record per product, below this
-// batch: observers of small runs (spz_profile_*) see there what they always saw. The row-tile
-// path is the faster one on both sides of the line (256-128 bf16, 45 inputs, two streams:
-// layer by layer 198 us a step at 512 rows and 213 us at 1536, 62 us there in row tiles).
+// The batches that take row tiles. Figures: step time layer by layer over step time in row
+// tiles, both of the present code.
+//
+// bfloat16, below: SAC networks whose layers all have mask bits (128-multiple widths) go layer
+// by layer, with the row split and one timing record per product that callers select and read
+// there (spz_profile_*, actor_row_split), below 1024 rows. Row tiles are the faster path on both
+// sides of that line (256-256, 17 inputs: 4.1 at 256, 3.6 at 1023, 3.8 at 2048 rows).
+//
+// bfloat16, above: a tile reads every weight through its CU's vector L1, where the large-tile
+// product of a 128-multiple layer reads it once a 256-row tile. 512-wide layers in 32-row tiles
+// (where 64 rows do not fit LDS) lose from two tiles a CU and half on: 512-512-512, 376 inputs, 1.08
+// at 16384 and 0.81 at 32768 rows; four layers 1.28 at 8192 and 1.03, six 1.02 and 0.92. In
+// 64-row tiles, 512 wide or with inputs wider than the layers: 512-512-512, 17 inputs, 1.00 at
+// 65536 and 0.96 above, 256-512, 376 inputs, 1.02 and 0.92, 256-256, 376 inputs, 1.13 and 0.99,
+// four layers of 512, 120 inputs, 1.00 at 32768 and 0.87. Others stay ahead (at 131072 rows 128-128
+// with 376 inputs 1.14, 384-384-384 1.16 to 1.39, 256-256-256 with 17 inputs 1.18, 480-480-480 on
+// the generic products 1.07 to 1.5).
+//
+// float32, below: few tiles leave most CUs idle, and a tile's chain of products takes the time
+// it takes; layer by layer each product spreads over the chip, bound by its launch. The chain
+// loses where a weight has more than some 150 thousand elements (400-300 with 376 inputs: 416 x
+// 416): both halves one after the other (sequential) 0.79 at 256, 0.95 at 2048, 1.20 at 4096
+// rows; on two streams replayed from graphs SAC 0.93, 0.99 at 1024, 1.15 at 2048, TD3 0.84,
+// 0.89, 1.04. Smaller weights: 400-300 with 17 inputs 0.95 to 1.5, 320-320 1.03 and more. Eager
+// SAC on two streams, whose launches the host has to keep up with: two layers 1.13 there, 1.14
+// and 0.97 for 512-512 with 17 and 376 inputs, three of 512 0.99 and 0.89. A SAC snapshot step on
+// one stream runs its launches one after the other and is always the slower one (512-512-512
+// with 376 inputs 1.12 at 256 rows).
 constexpr int ROW_MIN_SPLIT_BATCH = 1024;
+constexpr int64_t ROW_LONG_WEIGHT = 150000, ROW_LONG_WEIGHT_EAGER = 200000;
+RowRange row_range(const spz_ctx* c) {
+  RowRange r{1, INT32_MAX};
+  const bool seq = c->hp.ordering == SPZ_ORDER_SEQUENTIAL, two = c->hp.n_streams == 2 && !seq;
+  if (c->bf16) {
+    bool tiles = true, wide = false;   // every layer on the large-tile product; one of them 512 wide
+    for (int h : c->hidden) {
+      tiles = tiles && pad32(h) % 128 == 0;
+      wide = wide || pad32(h) == 512;
+    }
+    const bool tall = row_nets(c, 2) > 0;   // 64-row tiles fit
+    if (tiles && !c->td3) r.lo = ROW_MIN_SPLIT_BATCH;
+    const bool deep = c->hidden.size() > 3;
+    if (wide && !tall) r.hi = deep ? 8192 : 16384;
+    else if (tiles && (wide || !tall || (c->Ka > c->hmax && c->hmax >= 256))) r.hi = wide && deep ? 32768 : 65536;
+    return r;
+  }
+  const bool eager = two && !c->td3 && !c->hp.graphs;
+  if (!c->td3 && !seq && (!two || (eager && c->hidden.size() <= 2))) return r;
+  int64_t largest = 0;
+  for (const Lay& L : c->net[1].L) largest = std::max(largest, (int64_t)L.in_p * L.out_p);
+  if (largest > (eager ? ROW_LONG_WEIGHT_EAGER : ROW_LONG_WEIGHT)) r.lo = seq ? 3072 : 2048;
+  return r;
+}
 bool row_batch(const spz_ctx* c, int batch) {
-  if (!c->rows_ok) return false;
-  if (!c->bf16 || c->td3) return true;
-  for (int h : c->hidden)
-    if (pad32(h) % 128) return true;
-  return batch >= ROW_MIN_SPLIT_BATCH;
+  return c->rows_ok && batch >= c->row_range.lo && batch <= c->row_range.hi;
 }
 
 // Tile height (in units of 32 rows) for a batch. A bf16 product is bound by the weights' way
@@ -1280,7 +1331,7 @@ hipError_t refresh_packed(spz_ctx* c, hipStream_t s) {
 
 int setup_rows(spz_ctx* c) {
   const size_t e = es(c);
-  const int64_t Bp = c->Bp;
+  const int64_t Bp = c->rows_Bp;
   const int nh = (int)c->hidden.size(), nl = nh + 1;
   const int pa = c->net[0].L.back().out_p;
   const size_t nt = (size_t)Bp / ROW_MIN_TILE;   // the most tiles
@@ -1672,7 +1723,7 @@ hipError_t refresh_images(spz_ctx* c, hipStream_t s) {
 // Operand images and workspaces of the layer-by-layer path.
 int setup_layers(spz_ctx* c) {
   const size_t e = es(c);
-  const int64_t Bp = c->Bp;
+  const int64_t Bp = c->layers_Bp;
   const int nh = (int)c->hidden.size();
   if (c->bf16) {
     CK(dalloc_t(c, &c->Pb, (size_t)c->n_arena * 2));
@@ -1772,9 +1823,11 @@ int setup_layers(spz_ctx* c) {
     CK(dalloc_t(c, &c->rbits2, (size_t)Bp * (c->hmax / 32) * 4));
   }
   // deferred-reduction workspaces, sized for the created batch (spz_set_batch checks
-  // that a smaller one fits)
+  // that a smaller one fits), or for every batch that comes here where row tiles take others
   for (int q = 0; q < 2; ++q) {
     c->red[q].cap = red_need(c, q, (int)Bp);
+    for (int b = 256; b < Bp && c->rows_ok; b += 256)
+      if (!row_batch(c, b - 255) || !row_batch(c, b)) c->red[q].cap = std::max(c->red[q].cap, red_need(c, q, b));
     CK(dalloc_t(c, &c->red[q].base, (size_t)c->red[q].cap * 4));
   }
   return SPZ_OK;
@@ -1819,9 +1872,14 @@ int setup(spz_ctx* c) {
   CK(dalloc_t(c, &c->se, (size_t)Bp * c->A * 4));
   CK(dalloc_t(c, &c->lm, (size_t)Bp * c->A * 4));
   CK(dalloc_t(c, &c->da1, (size_t)Bp * c->Ap * 4));
-  c->rows_ok = row_fits(c);
-  c->layers_ok = !row_batch(c, 1);   // some batch size takes the layer-by-layer path
+  // Either path's buffers hold the batches up to the created one that take it.
+  c->row_range = row_range(c);
+  c->rows_ok = row_fits(c) && c->row_range.lo <= c->B;
+  c->layers_ok = !row_batch(c, 1) || !row_batch(c, c->B);
   c->rows_on = row_batch(c, c->B);
+  auto pad256 = [](int64_t x) { return (x + 255) / 256 * 256; };
+  if (c->rows_ok) c->rows_Bp = std::min(Bp, pad256(c->row_range.hi));
+  if (c->layers_ok) c->layers_Bp = c->rows_on ? std::min(Bp, pad256(c->row_range.lo - 1)) : Bp;
   c->last_rows = c->rows_on;   // debug reads before the first step look at buffers that are there
   if (c->rows_ok) {
     const int rc = setup_rows(c);
@@ -2170,7 +2228,7 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
   }
   // Chunks of at most the created batch (the actor workspaces' row count) and of the
   // observation staging area.
-  const int64_t chunk = std::min<int64_t>(c->Bpmax, c->stage_rows) / 256 * 256;
+  const int64_t chunk = std::min<int64_t>(c->rows_on ? c->Bpmax : c->layers_Bp, c->stage_rows) / 256 * 256;
   const int saveB = c->B, saveBp = c->Bp;
   const int pa = c->net[0].L.back().out_p;
   hipStream_t s = c->sc;
@@ -2424,7 +2482,8 @@ int spz_set_batch(spz_ctx* c, int32_t batch) {
   if (!c) return set_err(nullptr, SPZ_EINVAL, "spz_set_batch: NULL context");
   if (batch < 1 || batch > c->Bmax) return set_err(c, SPZ_EINVAL, "spz_set_batch: batch out of [1, created batch]");
   const int Bp = (batch + 255) / 256 * 256;
-  for (int q = 0; q < 2 && c->layers_ok; ++q)
+  const bool rows = row_batch(c, batch);
+  for (int q = 0; q < 2 && !rows; ++q)
     if (red_need(c, q, Bp) > c->red[q].cap)
       return set_err(c, SPZ_EINVAL, "spz_set_batch: reduction workspace too small for this batch");
   CK(hipSetDevice(c->hp.device));
@@ -2435,15 +2494,15 @@ int spz_set_batch(spz_ctx* c, int32_t batch) {
   if (Bp > batch) {
     const size_t e = es(c);
     const size_t pad = (size_t)(Bp - batch);
-    for (void* x : {c->xsa, c->xs2, c->xsp})
+    for (void* x : {c->xsa, c->xs2, rows ? nullptr : c->xsp})
       if (x) CK(hipMemset(static_cast<uint8_t*>(x) + (size_t)batch * c->Kc * e, 0, pad * c->Kc * e));
     const int pa = c->net[0].L.back().out_p;
-    if (c->dzh) CK(hipMemset(static_cast<uint8_t*>(c->dzh) + (size_t)batch * pa * e, 0, pad * pa * e));
+    if (!rows) CK(hipMemset(static_cast<uint8_t*>(c->dzh) + (size_t)batch * pa * e, 0, pad * pa * e));
   }
   c->B = batch;
   c->Bp = Bp;
-  if (row_batch(c, batch) != c->rows_on) {   // a step keeps only its own path's images current
-    c->rows_on = !c->rows_on;
+  if (rows != c->rows_on) {   // a step keeps only its own path's images current
+    c->rows_on = rows;
     CK(refresh_images(c, c->sc));
     CK(hipStreamSynchronize(c->sc));
   }
@@ -2674,7 +2733,8 @@ int spz_debug_read(spz_ctx* c, int32_t what, void* out, int64_t bytes) {
       std::vector<float> rr(B), dd(B);
       CK(hipMemcpy(xa.data(), c->xsa, xa.size(), hipMemcpyDeviceToHost));
       CK(hipMemcpy(x2.data(), c->xs2, x2.size(), hipMemcpyDeviceToHost));
-      if (!two) CK(hipMemcpy(ab.data(), c->abuf, ab.size(), hipMemcpyDeviceToHost));
+      // (a step's own buffers: those past its path's batches have no row of it)
+      if (!two) CK(hipMemcpy(ab.data(), c->abuf, (size_t)std::min(B, c->layers_Bp) * c->A * e, hipMemcpyDeviceToHost));
       CK(hipMemcpy(rr.data(), c->r, B * 4, hipMemcpyDeviceToHost));
       CK(hipMemcpy(dd.data(), c->d, B * 4, hipMemcpyDeviceToHost));
       auto val = [&](const std::vector<uint8_t>& v, int64_t i) {
@@ -2701,7 +2761,7 @@ int spz_debug_read(spz_ctx* c, int32_t what, void* out, int64_t bytes) {
       const bool two = !c->td3 && !c->row_split && !c->last_rows;
       std::vector<float> d1((size_t)B * c->Ap), d2(two ? (size_t)B * c->Ap : 0);
       CK(hipMemcpy(d1.data(), c->da1, d1.size() * 4, hipMemcpyDeviceToHost));
-      if (two) CK(hipMemcpy(d2.data(), c->da2, d2.size() * 4, hipMemcpyDeviceToHost));
+      if (two) CK(hipMemcpy(d2.data(), c->da2, (size_t)std::min(B, c->layers_Bp) * c->Ap * 4, hipMemcpyDeviceToHost));
       for (int64_t b = 0; b < B; ++b)
         for (int j = 0; j < c->A; ++j)
           f[b * c->A + j] = d1[b * c->Ap + j] + (two ? d2[b * c->Ap + j] : 0.0f);
@@ -2791,7 +2851,26 @@ int spz_profile_read(spz_ctx* c, spz_kernel_stat* out, int32_t max, int32_t* n_o
 
 const char* spz_last_error(const spz_ctx* c) { return c ? c->err.c_str() : tl_err.c_str(); }
 
-// Test hook: no HIP call, no context.
+// Test hooks: no HIP call, no context.
+int spzt_row_range(int32_t td3, int32_t bf16, int32_t sequential, int32_t n_streams, int32_t graphs, int32_t obs_dim,
+                   int32_t act_dim, const int32_t* hidden, int32_t n_hidden, int32_t* lo, int32_t* hi) {
+  if (obs_dim < 1 || act_dim < 1 || !hidden || n_hidden < 1 || n_hidden > 6 || !lo || !hi) return SPZ_EINVAL;
+  spz_ctx c;
+  c.O = obs_dim;
+  c.A = act_dim;
+  c.hidden.assign(hidden, hidden + n_hidden);
+  c.td3 = td3 != 0;
+  c.bf16 = bf16 != 0;
+  c.hp.ordering = sequential ? SPZ_ORDER_SEQUENTIAL : SPZ_ORDER_SNAPSHOT;
+  c.hp.n_streams = n_streams;
+  c.hp.graphs = graphs;
+  plan_layout(&c);
+  const RowRange r = row_fits(&c) ? row_range(&c) : RowRange{0, 0};
+  *lo = r.lo;
+  *hi = r.hi;
+  return SPZ_OK;
+}
+
 int spzt_row_workspace(int32_t td3, int32_t bf16, int32_t obs_dim, int32_t act_dim, const int32_t* hidden,
                        int32_t n_hidden, int32_t created, int32_t batch, int64_t* cap, int64_t* need) {
   if (obs_dim < 1 || act_dim < 1 || !hidden || n_hidden < 1 || n_hidden > 6 || batch < 1 || created < batch || !cap ||
@@ -2804,9 +2883,11 @@ int spzt_row_workspace(int32_t td3, int32_t bf16, int32_t obs_dim, int32_t act_d
   c.td3 = td3 != 0;
   c.bf16 = bf16 != 0;
   plan_layout(&c);
+  c.row_range = row_range(&c);
+  c.rows_ok = row_fits(&c);
   *cap = *need = 0;
-  if (!row_fits(&c)) return SPZ_OK;
-  *cap = row_wgrad_cap(&c, (created + 255) / 256 * 256);
+  if (!row_batch(&c, batch)) return SPZ_OK;
+  *cap = row_wgrad_cap(&c, (std::min(created, c.row_range.hi) + 255) / 256 * 256);
   for (int tm = 1; tm <= (c.bf16 ? 2 : 1); ++tm)
     for (int what = 1; what <= 3; ++what)
       *need = std::max(*need, row_wgrad_floats(&c, what & 1, what & 2, row_tile_count(batch, tm) * 32 * tm / row_ks(&c)));

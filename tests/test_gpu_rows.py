@@ -178,3 +178,62 @@ def test_adam_and_polyak_round_as_written(prec, hidden):
             t = (wide(tau) * g.read_params(k).astype(wide) + ((one - tau) * old["t" + k]).astype(wide)).astype(f32)
             assert np.array_equal(g.read_params("t" + k), t), k
     g.close()
+
+
+# Networks and batches on either side of the lines between the paths, where the chip is left
+# idle by too few tiles (float32) or 512-wide weights pass through too many CUs (bfloat16).
+F400 = Workload("fp32_400_300_seq", "sac", 376, 6, (400, 300), 3100, 20000, "fp32", 10, target_entropy=-6.0,
+                ordering="sequential")
+B512 = Workload("bf16_512_x3", "sac", 376, 17, (512, 512, 512), 17000, 20000, "bf16", 10, target_entropy=-17.0)
+SIDES = [(F400, 300, False), (F400, 3071, False), (F400, 3072, True), (F400.replace(ordering="snapshot"), 300, True),
+         (F400.replace(algo="td3", learn_alpha=False, alpha_init=0.0, ordering="snapshot"), 300, False),
+         (B512, 1023, False), (B512, 1024, True), (B512, 16384, True), (B512, 16385, False)]
+
+
+@pytest.mark.parametrize("w,b,rows", SIDES, ids=["%s-%s-%s-%d" % (w.name, w.algo, w.ordering, b) for w, b, _ in SIDES])
+def test_path_of_a_batch_and_its_results(w, b, rows):
+    """The path a batch takes, and the same results from a context created for more rows (which
+    has run another batch, on the other path where there is one) as from one created for b."""
+    out = []
+    for created in (w.batch, b):
+        g = make_gpu(w.replace(batch=created))
+        g.buffer_push(*synth.workload_rows(w, 0, 5000, 0))
+        if created != b:
+            keep = {k: g.read_params(k) for k in ("actor", "critic1", "critic2", "tcritic1", "tcritic2")}
+            g.update(1)
+            g.set_batch(2000)
+            g.update(1)
+            for k in keep:
+                g.write_params(k, keep[k])
+            for k in ("actor", "critic1", "critic2", "log_alpha"):
+                for m in ("m_", "v_"):
+                    g.write_params(m + k, np.zeros(g.param_count(m + k), np.float32))
+            g.write_params("log_alpha", np.full(1, np.log(w.alpha_init) if w.algo == "sac" else 0.0, np.float32))
+            if w.algo == "td3":
+                g.write_params("tactor", keep["actor"])
+            g.set_batch(b)
+            g.set_step(0)
+        g.profile_enable(True, 1000)
+        g.update(2)
+        assert ("row_step" in {s["name"] for s in g.profile_read()}) == rows
+        out.append({k: g.read_params(k) for k in ("actor", "critic1", "critic2", "tcritic1", "m_critic2", "log_alpha")})
+        out[-1].update(rec=g.read_losses(1, 2), act=g.act(synth.workload_rows(w, 0, 70, 3)[0]), da=g.debug_rows("daction"))
+        g.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.parametrize("n_streams", [1, 2])
+def test_debug_reads_after_a_larger_batch_was_set(n_streams):
+    """A context whose layer buffers hold fewer rows than the batch now set: debug reads give the
+    last step's rows and end with the buffers."""
+    g = make_gpu(F400, n_streams=n_streams)
+    g.buffer_push(*synth.workload_rows(F400, 0, 5000, 0))
+    g.set_batch(200)
+    g.update(1)
+    small = [np.array(x) for x in g.debug_batch()] + [g.debug_rows("daction")]
+    g.set_batch(3100)
+    large = list(g.debug_batch()) + [g.debug_rows("daction")]
+    g.close()
+    for a, b in zip(small, large):
+        assert len(b) == 3100 and np.array_equal(a, b[:200])

@@ -1,6 +1,6 @@
-"""The row-tile path's weight-gradient workspace holds every launch a context can make: the
-critics', the actor's or both, at every batch up to the created one. Host arithmetic of the
-library itself (no GPU)."""
+"""The batches that take the row-tile path, and its weight-gradient workspace, which holds every
+launch a context can make: the critics', the actor's or both, at every batch up to the created
+one. Host arithmetic of the library itself (no GPU)."""
 import ctypes
 import math
 import os
@@ -51,3 +51,29 @@ def test_workspace_covers_every_launch_and_batch(workspace):
         fits += need > 0
         assert cap >= need, case
     assert fits > 20000
+
+
+@pytest.mark.parametrize("td3,bf16,seq,streams,graphs,obs,hidden,expect", [
+    # float32: everything, but for long weights with few tiles
+    (0, 0, 0, 2, 0, 17, (256, 256), (1, 2**31 - 1)), (0, 0, 1, 2, 0, 376, (256, 256), (1, 2**31 - 1)),
+    (0, 0, 1, 2, 0, 17, (400, 300), (1, 2**31 - 1)), (0, 0, 1, 2, 0, 376, (400, 300), (3072, 2**31 - 1)),
+    (0, 0, 0, 2, 0, 376, (400, 300), (1, 2**31 - 1)), (0, 0, 0, 2, 1, 376, (400, 300), (2048, 2**31 - 1)),
+    (0, 0, 0, 1, 1, 376, (512, 512, 512), (1, 2**31 - 1)), (0, 0, 0, 2, 0, 17, (512, 512, 512), (2048, 2**31 - 1)),
+    (1, 0, 0, 1, 0, 376, (400, 300), (2048, 2**31 - 1)), (1, 0, 1, 1, 0, 17, (512, 512), (3072, 2**31 - 1)),
+    # bfloat16: ragged layers everywhere; 128-multiple ones up to where a tile's weights cost most
+    (0, 1, 0, 2, 0, 376, (400, 300), (1, 2**31 - 1)), (0, 1, 0, 2, 0, 17, (256, 256), (1024, 2**31 - 1)),
+    (0, 1, 0, 2, 0, 376, (256, 256), (1024, 65536)), (1, 1, 0, 2, 0, 376, (256, 256), (1, 65536)),
+    (0, 1, 0, 2, 0, 376, (128, 128), (1024, 2**31 - 1)), (0, 1, 0, 2, 0, 17, (512,) * 4, (1024, 32768)),
+    (0, 1, 0, 2, 0, 17, (512, 512), (1024, 65536)), (0, 1, 0, 2, 0, 376, (512, 512), (1024, 16384)),
+    (1, 1, 0, 2, 0, 376, (512, 512, 512), (1, 16384)), (0, 1, 0, 2, 0, 376, (512,) * 6, (1024, 8192)),
+    (0, 1, 0, 2, 0, 376, (512, 480, 512), (1, 16384)), (0, 1, 0, 2, 0, 376, (384, 384, 384), (1024, 2**31 - 1)),
+    # past the tiles
+    (0, 1, 0, 2, 0, 17, (640,), (0, 0)), (0, 0, 0, 2, 0, 3000, (64, 64), (0, 0))])
+def test_batches_of_the_row_tile_path(workspace, td3, bf16, seq, streams, graphs, obs, hidden, expect):
+    from paper_2312_06126_amd import spz
+    i32 = ctypes.c_int32
+    lo, hi = i32(), i32()
+    h = (i32 * len(hidden))(*hidden)
+    assert spz.load().spzt_row_range(td3, bf16, seq, streams, graphs, obs, 6, h, len(hidden), ctypes.byref(lo),
+                                     ctypes.byref(hi)) == 0
+    assert (lo.value, hi.value) == expect
