@@ -224,8 +224,8 @@ int spz_synchronize(spz_ctx* ctx);
  * counter `counter` (step word), element index row * act_dim + j, so a call is
  * reproducible from (seed, counter). TD3: tanh of the actor output (stochastic must
  * be 0; samplers add their own exploration noise). Uses the current online actor
- * with the context's GEMM precision; rows are processed in chunks of the created
- * batch. Waits for the context's outstanding work; synchronous.
+ * with the context's GEMM precision; rows are processed in chunks of at most the
+ * created batch. Waits for the context's outstanding work; synchronous.
  * Errors: SPZ_EINVAL, SPZ_EHIP. */
 int spz_act(spz_ctx* ctx, const float* obs, int64_t n, int32_t stochastic, uint32_t counter, float* act);
 
@@ -240,7 +240,8 @@ int spz_act(spz_ctx* ctx, const float* obs, int64_t n, int32_t stochastic, uint3
  * and shared by every call on that GPU: calls that overlap on one GPU (other streams,
  * other threads, other contexts) race, so order them on one stream or synchronize
  * between them. The call writes every scratch byte it reads, so the previous call's
- * contents do not matter. (Networks on the row-tile path keep these values on chip.) n is limited by that array: at most the largest multiple
+ * contents do not matter. (Calls that take row tiles keep these values on chip and do not
+ * touch the array; which do may change.) n is limited by that array: at most the largest multiple
  * of 256 rows with e * (pad32(obs_dim) + 2 * max_l pad32(hidden[l])) + 4 * pad32(out)
  * bytes per row (e = 2 for bf16 GEMM operands, 4 for fp32; out = 2*act_dim for SAC,
  * act_dim for TD3), plus alignment, within 64 MiB; larger n gives SPZ_EINVAL with

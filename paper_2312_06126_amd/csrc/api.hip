@@ -1090,6 +1090,14 @@ RowRange row_range(const spz_ctx* c) {
   if (largest > (eager ? ROW_LONG_WEIGHT_EAGER : ROW_LONG_WEIGHT)) r.lo = seq ? 3072 : 2048;
   return r;
 }
+// Products a row of the actor, and up to how many a float32 sampler-action call always takes row
+// tiles (row_act_on).
+constexpr int64_t ROW_ACT_SHORT = 120000;
+int64_t row_act_macs(const spz_ctx* c) {
+  int64_t n = 0;
+  for (const Lay& L : c->net[0].L) n += (int64_t)L.in_p * L.out_p;
+  return n;
+}
 bool row_batch(const spz_ctx* c, int batch) {
   return c->rows_ok && batch >= c->row_range.lo && batch <= c->row_range.hi;
 }
@@ -1518,6 +1526,28 @@ hipError_t row_update(spz_ctx* c, bool crit, bool act, const FinishArgs* fin, co
                [&] { return launch_row_adam(c->bf16, p, s); });
 }
 
+// Whether a sampler-action call for n observations takes row tiles. The choice is the call's, not
+// its chunks', so that spz_act and spz_act_noalloc give the same bits. bfloat16: always (1.1 to
+// 2.7 times layer by layer over 1 to 12288 observations). float32: a tile's chain of products
+// takes the time it takes on a CU's float32 matrix cores (256-256, 17 inputs 19 us, 400-300 33,
+// with 376 inputs 51, 512-512-512 72), while few observations layer by layer spread over the
+// chip. Layer by layer over row tiles, by the actor's products a row:
+//   256-256, 17 inputs (82 thousand)     1.14 at 1, 1.31 at 2048, 1.35 at 12288 observations
+//   256-256, 376 inputs (180 thousand)   0.89 at 1, 0.99 at 2048, 1.22 at 4096
+//   400-300, 17 inputs (157 thousand)    0.79 at 1, 0.95 at 2048, 1.19 at 4096
+//   400-300, 376 inputs (313 thousand)   0.64 at 1, 0.74 at 2048, 1.05 at 4096, 1.41 at 8192
+//   512-512-512, 376 inputs (737)        0.54 at 1, 0.84 at 4096, 1.26 at 8192
+// Past 8192 observations (a tile on each of 256 CUs) the tiles come in rounds, and a last one
+// that is mostly empty costs more than the 1.3 a full one gains.
+bool row_act_on(const spz_ctx* c, int64_t n) {
+  if (!c->rows_on || c->bf16) return c->rows_on;
+  const int64_t macs = row_act_macs(c), round = 256 * 32;
+  if (macs <= ROW_ACT_SHORT) return true;
+  if (n < (macs <= 200000 ? 2048 : macs <= 400000 ? 4096 : 5120)) return false;
+  const int64_t rounds = (n + round - 1) / round;
+  return rounds == 1 || 10 * rounds * round <= 13 * n;
+}
+
 // Sampler actions for n observation rows in device memory.
 hipError_t row_act(spz_ctx* c, const float* obs, int n, int64_t row0, bool stochastic, uint32_t counter, float* act,
                    hipStream_t s) {
@@ -1833,6 +1863,19 @@ int setup_layers(spz_ctx* c) {
   return SPZ_OK;
 }
 
+// The actor's forward buffers alone, for sampler-action calls layer by layer in a context whose
+// steps all take row tiles.
+constexpr int64_t ACT_ROWS = 5120;
+int setup_act(spz_ctx* c) {
+  const size_t e = es(c);
+  const int64_t Bp = c->layers_Bp = std::min<int64_t>(c->Bp, ACT_ROWS);
+  CK(dalloc(c, &c->xsp, (size_t)Bp * c->Kc * e));
+  CK(dalloc_t(c, &c->z, (size_t)Bp * c->net[0].L.back().out_p * 4));
+  c->ha.assign(c->hidden.size(), nullptr);
+  for (size_t l = 0; l < c->hidden.size(); ++l) CK(dalloc(c, &c->ha[l], (size_t)Bp * pad32(c->hidden[l]) * e));
+  return SPZ_OK;
+}
+
 constexpr size_t PIN_BYTES = (size_t)1 << 20;
 // Observations of up to this size reach the sampler-action kernel through pinned memory;
 // above it the copy engine's rate outweighs its latency.
@@ -1887,6 +1930,9 @@ int setup(spz_ctx* c) {
   }
   if (c->layers_ok) {
     const int rc = setup_layers(c);
+    if (rc) return rc;
+  } else if (!c->bf16 && row_act_macs(c) > ROW_ACT_SHORT) {
+    const int rc = setup_act(c);
     if (rc) return rc;
   }
   // one partial per 256-row block, or per wave of a row tile
@@ -2228,7 +2274,8 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
   }
   // Chunks of at most the created batch (the actor workspaces' row count) and of the
   // observation staging area.
-  const int64_t chunk = std::min<int64_t>(c->rows_on ? c->Bpmax : c->layers_Bp, c->stage_rows) / 256 * 256;
+  const bool rows_act = row_act_on(c, n);
+  const int64_t chunk = std::min<int64_t>(rows_act ? c->Bpmax : c->layers_Bp, c->stage_rows) / 256 * 256;
   const int saveB = c->B, saveBp = c->Bp;
   const int pa = c->net[0].L.back().out_p;
   hipStream_t s = c->sc;
@@ -2256,7 +2303,7 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
       }
       if (e != hipSuccess) rc = set_err(c, SPZ_EHIP, std::string("spz_act: ") + hipGetErrorString(e));
     };
-    if (c->rows_on) {
+    if (rows_act) {
       if (e == hipSuccess) e = row_act(c, obs_dev, m, r0, stochastic != 0, counter, act_dev, s);
       finish();
       continue;
@@ -2324,7 +2371,7 @@ int spz_act_noalloc(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic,
   uint8_t* base = static_cast<uint8_t*>(g_scratch_ptr[c->hp.device]);
   if (!base) return set_err(c, SPZ_EHIP, "spz_act_noalloc: scratch address not initialised");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (c->rows_on) {   // needs no scratch
+  if (row_act_on(c, n)) {   // needs no scratch
     CK(row_act(c, obs, (int)n, 0, stochastic != 0, counter, act, s));
     return SPZ_OK;
   }

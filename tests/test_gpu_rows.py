@@ -237,3 +237,27 @@ def test_debug_reads_after_a_larger_batch_was_set(n_streams):
     g.close()
     for a, b in zip(small, large):
         assert len(b) == 3100 and np.array_equal(a, b[:200])
+
+
+@pytest.mark.parametrize("obs_dim,hidden,created", [(17, (400, 300), 1000), (17, (400, 300), 20000), (376, (256, 256), 700),
+                                                    (376, (400, 300), 6000), (13, (64, 64), 300)])
+def test_float32_actions_on_either_path(obs_dim, hidden, created):
+    """float32 action calls from one observation to two rounds of tiles, on both sides of each
+    line between the paths: spz_act (in chunks) and spz_act_noalloc give the same bits, both
+    within float32 rounding of the actor in 64 bits (the bound of the sampler parity test)."""
+    from oracle import Oracle
+    w = RAGGED.replace(name="act", obs_dim=obs_dim, hidden=hidden, batch=created)
+    g = make_gpu(w)
+    o = Oracle(w.obs_dim, w.act_dim, w.hidden, w.batch, w.hparams(), 1)
+    obs = np.random.default_rng(5).standard_normal((13000, obs_dim)).astype(np.float32)
+    ref = o.act(obs.astype(np.float64), True, 9)
+    dev = torch.from_numpy(obs).cuda()
+    for n in (1, 33, 2047, 2048, 4095, 4096, 8192, 8225, 13000):
+        out = torch.empty(n, w.act_dim, device="cuda")
+        torch.cuda.synchronize()
+        g.act_noalloc(dev.data_ptr(), n, out.data_ptr(), True, 9)
+        torch.cuda.synchronize()
+        host = g.act(obs[:n], True, 9)
+        assert np.array_equal(host, out.cpu().numpy()), n
+        assert np.abs(host - ref[:n]).max() <= 1e-5, n
+    g.close()
