@@ -777,13 +777,32 @@ __device__ inline void warm_l2(const RowArgs& g, int part, int tid, uint32_t (&t
   }
 }
 
+// Sampler actions from the actor's output in Z.
+template <typename T, int TM>
+__device__ inline void sampler_actions(const RowArgs& g, const Lds& L, int64_t tile, int tid) {
+  constexpr int BM = 32 * TM;
+  for (int e = tid; e < BM * g.A; e += ROW_THREADS) {
+    const int r = e / g.A, j = e - r * g.A;
+    const int64_t b = tile * BM + r;
+    if (b >= g.B) break;
+    const float* z = L.z() + r * g.zp;
+    const int64_t i = b * g.A + j;
+    float u = z[j];
+    if (g.stochastic)
+      u += expf(clamp_keep_nan(z[g.A + j], g.lmin, g.lmax)) * normal_at(g.seed, (uint64_t)(g.row0 * g.A + i), g.counter, P_ACT);
+    g.act[i] = tanhf(u);
+  }
+}
+
+// ACT: sampler actions, a kernel of their own so that neither's operations press on the other's
+// registers (in one kernel: 24 bytes of scratch in float32, or 2% of a step of 400-300 (TD3) at 32768
+// rows in other arrangements of the same code).
 // 32-row tiles: 128 registers, two workgroups per CU where their LDS allows it (where it does
 // not, 155 registers are slower: 400-300 fp32 1067 against 1028 us); 64-row tiles take the LDS
 // of a CU.
-template <typename T, int TM>
+template <typename T, int TM, bool ACT>
 __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs args) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  constexpr int BM = 32 * TM;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = (int)blockIdx.x >= args.tiles ? 1 : 0;
   const int64_t tile = (int)blockIdx.x - part * args.tiles;
@@ -820,40 +839,30 @@ __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs a
         else if (o.split > 1 || o.from_h) __syncthreads();
         break;
       }
-      case ROW_LOAD: {
-        uint32_t t[WARM + 1];
-        const bool warm = g.warm_lines > 0 && o.flags != ROW_LOAD_SA;
-        if (warm) warm_l2(g, part, tid, t);
-        load_tile<T, TM>(g, o, L, tile, tid);
-        if (warm) {
+      case ROW_LOAD:
+        if constexpr (!ACT) {
+          uint32_t t[WARM + 1];
+          const bool warm = g.warm_lines > 0 && o.flags != ROW_LOAD_SA;
+          if (warm) warm_l2(g, part, tid, t);
+          load_tile<T, TM>(g, o, L, tile, tid);
+          if (warm) {
 #pragma unroll
-          for (int i = 0; i <= WARM; ++i) asm volatile("" ::"v"(t[i]));
+            for (int i = 0; i <= WARM; ++i) asm volatile("" ::"v"(t[i]));
+          }
         }
         break;
-      }
-      case ROW_OBS: load_obs<T, TM>(g, L, tile, tid); break;
-      case ROW_DOT: output_dot<T, TM>(g, o, L, tile, tid); break;
-      case ROW_DZ: output_backward<T, TM>(g, o, L, tile, net, slot, first, cnt, wpn, lane); break;
+      case ROW_OBS: if constexpr (ACT) load_obs<T, TM>(g, L, tile, tid); break;
+      case ROW_DOT: if constexpr (!ACT) output_dot<T, TM>(g, o, L, tile, tid); break;
+      case ROW_DZ: if constexpr (!ACT) output_backward<T, TM>(g, o, L, tile, net, slot, first, cnt, wpn, lane); break;
       case ROW_PACK:
-        for (int cb = wave; cb < o.nblk; cb += ROW_WAVES)
-          pack_block<T, TM>(o.from_h ? L.h<T>(0) : L.x<T>(), o.from_h ? g.ldh : g.ldx, o.nblk, cb, tile, o.pack[0],
-                            o.part[0], nullptr, nullptr, false, lane);
+        if constexpr (!ACT)
+          for (int cb = wave; cb < o.nblk; cb += ROW_WAVES)
+            pack_block<T, TM>(o.from_h ? L.h<T>(0) : L.x<T>(), o.from_h ? g.ldh : g.ldx, o.nblk, cb, tile, o.pack[0],
+                              o.part[0], nullptr, nullptr, false, lane);
         break;
-      case ROW_HEAD: head<T, TM>(g, o, L, tile, tid); break;
-      case ROW_HEAD_BWD: head_backward<T, TM>(g, o, L, tile, tid); break;
-      case ROW_ACT:
-        for (int e = tid; e < BM * g.A; e += ROW_THREADS) {
-          const int r = e / g.A, j = e - r * g.A;
-          const int64_t b = tile * BM + r;
-          if (b >= g.B) break;
-          const float* z = L.z() + r * g.zp;
-          const int64_t i = b * g.A + j;
-          float u = z[j];
-          if (g.stochastic)
-            u += expf(clamp_keep_nan(z[g.A + j], g.lmin, g.lmax)) * normal_at(g.seed, (uint64_t)(g.row0 * g.A + i), g.counter, P_ACT);
-          g.act[i] = tanhf(u);
-        }
-        break;
+      case ROW_HEAD: if constexpr (!ACT) head<T, TM>(g, o, L, tile, tid); break;
+      case ROW_HEAD_BWD: if constexpr (!ACT) head_backward<T, TM>(g, o, L, tile, tid); break;
+      case ROW_ACT: if constexpr (ACT) sampler_actions<T, TM>(g, L, tile, tid); break;
     }
     if (o.kind != ROW_PACK) __syncthreads();   // what a pack reads is overwritten only past a later barrier
   }
@@ -1104,16 +1113,16 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   }
 }
 
-template <typename T, int TM>
+template <typename T, int TM, bool ACT>
 hipError_t launch_rows_t(const RowArgs& g, size_t lds, hipStream_t s) {
   static std::atomic<bool> ready{false};
   if (!ready.load()) {
-    const hipError_t e = hipFuncSetAttribute((const void*)(k_rows<T, TM>),
+    const hipError_t e = hipFuncSetAttribute((const void*)(k_rows<T, TM, ACT>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     ready.store(true);
   }
-  (k_rows<T, TM>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
+  (k_rows<T, TM, ACT>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
   return hipGetLastError();
 }
 
@@ -1123,8 +1132,10 @@ hipError_t launch_rows(bool bf16, const RowArgs& g, size_t lds, hipStream_t s) {
   if (g.tiles < 1 || g.parts < 1 || g.parts > 2 || lds > 160 * 1024 || (g.tm != 1 && g.tm != 2) ||
       (!bf16 && g.tm != 1) || (int64_t)g.tiles * 32 * g.tm < g.B)
     return hipErrorInvalidValue;
-  if (!bf16) return launch_rows_t<float, 1>(g, lds, s);
-  return g.tm == 1 ? launch_rows_t<bf16_t, 1>(g, lds, s) : launch_rows_t<bf16_t, 2>(g, lds, s);
+  const bool act = g.obs != nullptr;
+  if (!bf16) return act ? launch_rows_t<float, 1, true>(g, lds, s) : launch_rows_t<float, 1, false>(g, lds, s);
+  if (g.tm == 1) return act ? launch_rows_t<bf16_t, 1, true>(g, lds, s) : launch_rows_t<bf16_t, 1, false>(g, lds, s);
+  return act ? launch_rows_t<bf16_t, 2, true>(g, lds, s) : launch_rows_t<bf16_t, 2, false>(g, lds, s);
 }
 
 hipError_t launch_row_wgrad(bool bf16, RowWArgs& w, hipStream_t s) {
