@@ -81,6 +81,17 @@ int spzt_reduce_jobs(int32_t n, const float* const* part, float* const* out, con
  */
 int spzt_bf16_round_check(uint64_t begin, uint64_t count, uint64_t* mismatches);
 /*
+ * The row-tile path's weight-gradient product of packed batch tensors a [rows, 32 mblk] and
+ * b [rows, 32 nblk] (device pointers; rows a multiple of 32): a tensor is 1 KB fragments, over
+ * its 32-column blocks, then over groups of KS rows (8 in float32, 16 in bfloat16); lane 32 h +
+ * r's 16 bytes of one are column r of the block, rows KS / 2 h + 0, 1, ... of the group. part
+ * [slices, mblk, nblk, 1024] float32 gets each slice's sums: four of rows 8 g + 4 h + 0 .. 3,
+ * column r, from element 256 g + 4 (32 h + r) of a block on. split (float32): 1 on bfloat16 parts,
+ * 0 on the float32 instructions. Synchronous.
+ */
+int spzt_row_wgrad(int32_t bf16, int32_t split, int32_t rows, int32_t mblk, int32_t nblk, int32_t slices,
+                   const void* a, const void* b, float* part);
+/*
  * The row-tile path's weight-gradient workspace of a context created for `created` rows:
  * *cap floats allocated, *need the most that a launch of the critics, of the actor or of
  * both writes at `batch` (<= created) rows. Both 0 where that batch does not take the path.

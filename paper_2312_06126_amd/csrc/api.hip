@@ -1487,6 +1487,7 @@ hipError_t row_update(spz_ctx* c, bool crit, bool act, const FinishArgs* fin, co
   RowWArgs W{};
   RowPArgs p{};
   W.groups = tiles * 32 * tm / row_ks(c);
+  W.split = c->B >= ROW_SPLIT_ROWS;
   const int slices = row_slices(row_tiles(c, crit, act), W.groups);
   int64_t off = 0;
   int index = 0;   // of the product in the work list

@@ -92,7 +92,12 @@ struct RowWJob {
   int mblk, nblk, bcb, slices, task0;
 };
 constexpr int MAX_ROW_WJOBS = 24;
-struct RowWArgs { RowWJob j[MAX_ROW_WJOBS]; int n, tasks, groups; int has_fin; FinishArgs fin; };
+// split (float32): the products run on bfloat16 parts of their operands, from ROW_SPLIT_ROWS
+// batch rows on. Of a few rows each product's own rounding counts, and the float32 instructions
+// are the nearer ones (one row: 1.03 times their distance from 64 bits, the largest element 1.4
+// times), while a tile that is mostly padding takes the same time either way (2 x 64: 15 us).
+constexpr int ROW_SPLIT_ROWS = 32;
+struct RowWArgs { RowWJob j[MAX_ROW_WJOBS]; int n, tasks, groups; int split; int has_fin; FinishArgs fin; };
 inline int row_wjob_tiles(int mblk, int nblk) { return ((mblk + 1) / 2) * ((nblk + 1) / 2); }
 // Sets the jobs' task0 and the task count.
 hipError_t launch_row_wgrad(bool bf16, RowWArgs& w, hipStream_t s);

@@ -45,16 +45,18 @@ __device__ inline void mma(f32x16& acc, const u32x4& a, const u32x4& b) {
   }
 }
 
-// Eight float32 values of a lane (two steps' fragments) as a sum of three bfloat16 each: the
-// rounded value, the rounded rest and the rest of that, 24 bits and exact (the last rest has
-// at most 8 significant bits).
+// Eight float32 values of a lane (two steps' fragments), 2^24 times each, as a sum of three
+// bfloat16: the rounded value, the rounded rest and the rest of that, 24 bits and exact (the last
+// rest has at most 8 significant bits, and the factor keeps it a normal number down to the
+// smallest normal value: without it values below 2^-109 lose bits).
+constexpr float SPLIT_SCALE = 0x1p24f;
 struct Split { u32x4 p[3]; };
 __device__ inline Split split(const u32x4& lo, const u32x4& hi) {
   Split s;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const f32x4 v = __builtin_bit_cast(f32x4, i < 2 ? lo : hi);
-    float a = v[2 * (i & 1)], b = v[2 * (i & 1) + 1];
+    float a = SPLIT_SCALE * v[2 * (i & 1)], b = SPLIT_SCALE * v[2 * (i & 1) + 1];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
       const uint32_t w = pack_bf16x2(a, b);
@@ -68,26 +70,24 @@ __device__ inline Split split(const u32x4& lo, const u32x4& hi) {
   return s;
 }
 
-// acc += A B^T over two float32 steps (16 deep) on the bfloat16 matrix instructions: the six
-// products of at most 2^-18 of the largest and above, smallest first (the three left out are
-// below 2^-25 of it). 6 x 32 clocks where the float32 instructions take 8 x 64. Infinite
-// values give NaN (the rest of an infinity is one): the caller checks. For weight gradients
-// only: their distance from 64 bits does not grow (five networks, three seeds, per tensor: 0.7
-// to 1.0 of the float32 instructions'), while input gradients on split operands, 3 - 4% faster
-// a step, put the first layer's bias gradient up to 1.6 times further off.
-__device__ inline void mma_split(f32x16& acc, const Split& a, const Split& b) {
+// A B^T over two float32 steps (16 deep) on the bfloat16 matrix instructions, 6 x 32 clocks where
+// the float32 instructions take 8 x 64: the products of the largest parts are added to `hi`, the
+// five of at most 2^-9 and at least 2^-18 of them to `lo` (the three left out are below 2^-26 of
+// them). With all six on one accumulator each of them would round the running sum; apart, only
+// the first does, once for 16 rows where the float32 instructions round it for every two.
+// Distance from 64 bits over that of the float32 instructions (128 x 128, masked gradients and
+// ReLU outputs, the sum over all elements): 0.91 at 4 rows, 0.56 at 32, 0.5 at 1000, 0.44 at 32768 and
+// 131072; on one accumulator 1.13, 1.12, 1.3, 1.5 and 1.9. One and two rows: see ROW_SPLIT_ROWS.
+// Weight gradients only: input gradients on split operands, 3 - 4% faster a step, put the first
+// layer's bias gradient up to 1.6 times further off.
+__device__ inline void mma_split(f32x16& hi, f32x16& lo, const Split& a, const Split& b) {
   constexpr int A[6] = {2, 0, 1, 1, 0, 0}, B[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[A[i]]),
-                                                  __builtin_bit_cast(bf16x8, b.p[B[i]]), acc, 0, 0, 0);
-}
-
-__device__ inline bool has_nan(const f32x16& a) {
-  bool n = false;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) n |= a[q] != a[q];
-  return n;
+  for (int i = 0; i < 6; ++i) {
+    f32x16& c = i < 5 ? lo : hi;
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a.p[A[i]]),
+                                                __builtin_bit_cast(bf16x8, b.p[B[i]]), c, 0, 0, 0);
+  }
 }
 
 __device__ inline void zero(f32x16& a) {
@@ -872,9 +872,10 @@ __global__ void __launch_bounds__(ROW_THREADS, TM == 1 ? 4 : 2) k_rows(RowArgs a
 // One wave takes 2 x 2 blocks of a product over one slice of the batch, fragments straight
 // from memory into registers: no LDS, no barriers. The four waves of a workgroup and its
 // neighbours on the same XCD take neighbouring tiles of the same slice, which share fragments.
-// float32 runs on split operands: 400-300 (TD3) at 32768 rows 218 -> 148 us for the critics'
-// and 146 -> 101 us for the actor's and critics' launch share against the float32 instructions
-// (then 132 and 86 us with twice the slices), 2 x 256 at 8192 rows 43 -> 33 us. bf16 is bound by
+// float32 runs on split operands (from ROW_SPLIT_ROWS rows on): 400-300 (TD3) at 32768 rows 272 us
+// for a launch of actor and critics and 182 for the critics' (float32 instructions 484 and 340), 2 x
+// 256 at 8192 rows 40 us (48); small parts on the main accumulators took 275, 172 and 36, further from
+// 64 bits than the float32 instructions (mma_split). bf16 is bound by
 // L2: 46 us for 550 MB at 2 x 256 (376 inputs), 16384 rows. (4 x 2 blocks a wave, 96 instead of
 // 128 bytes a block and row, is slower in both: the registers leave too little in flight.)
 template <typename T>
@@ -911,7 +912,8 @@ __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
     for (int i = 0; i < 4; ++i) zero(acc[i >> 1][i & 1]);
   };
   clear();
-  constexpr int PD = 4;
+  // Row groups in flight, twice: the float32 sums on split operands need the registers.
+  constexpr int PD = sizeof(T) == 2 ? 4 : 2;
   u32x4 f0[PD][4], f1[PD][4];
   auto load = [&](u32x4 (&f)[PD][4], int gr) {
 #pragma unroll
@@ -941,24 +943,31 @@ __global__ void __launch_bounds__(256, 2) k_row_wgrad(RowWArgs W) {
       for (int x = 0; x < 4; ++x) mma<T>(acc[x >> 1][x & 1], f[i][x >> 1], f[i][2 + (x & 1)]);
     }
   };
-  if constexpr (sizeof(T) == 2) {
+  if (sizeof(T) == 2 || !W.split) {
     run(exact);
-  } else {
+  } else if constexpr (sizeof(T) == 4) {
     // two row groups at a time on split operands (a slice has an even number of them)
-    run([&](const u32x4 (&f)[PD][4], int gr) {
+    f32x16 lo[2][2];
 #pragma unroll
-      for (int i = 0; i < PD; i += 2) {
-        if (gr + i >= g1) break;
-        const Split a0 = split(f[i][0], f[i + 1][0]), a1 = split(f[i][1], f[i + 1][1]);
-        const Split b0 = split(f[i][2], f[i + 1][2]), b1 = split(f[i][3], f[i + 1][3]);
-        mma_split(acc[0][0], a0, b0);
-        mma_split(acc[0][1], a0, b1);
-        mma_split(acc[1][0], a1, b0);
-        mma_split(acc[1][1], a1, b1);
-      }
+    for (int x = 0; x < 4; ++x) zero(lo[x >> 1][x & 1]);
+    run([&](const u32x4 (&f)[PD][4], int) {
+      const Split A[2] = {split(f[0][0], f[1][0]), split(f[0][1], f[1][1])};
+      const Split B[2] = {split(f[0][2], f[1][2]), split(f[0][3], f[1][3])};
+#pragma unroll
+      for (int x = 0; x < 4; ++x) mma_split(acc[x >> 1][x & 1], lo[x >> 1][x & 1], A[x >> 1], B[x & 1]);
     });
-    if (__any(has_nan(acc[0][0]) || has_nan(acc[0][1]) || has_nan(acc[1][0]) || has_nan(acc[1][1]))) {
-      clear();   // infinities or NaN: again in float32
+    float bad = 0.0f;   // NaN once a sum is an infinity or NaN
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      f32x16& c = acc[x >> 1][x & 1];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        c[q] = (c[q] + lo[x >> 1][x & 1][q]) * (1.0f / (SPLIT_SCALE * SPLIT_SCALE));
+        bad = fmaf(c[q], 0.0f, bad);
+      }
+    }
+    if (__any(bad != bad)) {
+      clear();   // infinities, NaN or sums past the scaled range: again in float32
       run(exact);
     }
   }

@@ -1,6 +1,6 @@
 // Test hooks (include/spz_testing.h): the GEMM kernels on caller-owned device memory.
 #include "../../include/spz_testing.h"
-#include "kernels.h"
+#include "rows.h"
 
 using namespace spz;
 
@@ -187,5 +187,19 @@ extern "C" int spzt_bf16_round_check(uint64_t begin, uint64_t count, uint64_t* m
   if (e == hipSuccess) e = hipMemcpy(&h, d, sizeof(h), hipMemcpyDeviceToHost);
   (void)hipFree(d);
   *mismatches = h;
+  return e == hipSuccess ? SPZ_OK : SPZ_EHIP;
+}
+
+extern "C" int spzt_row_wgrad(int32_t bf16, int32_t split, int32_t rows, int32_t mblk, int32_t nblk, int32_t slices,
+                              const void* a, const void* b, float* part) {
+  if (rows < 32 || rows % 32 || mblk < 1 || nblk < 1 || slices < 1 || !a || !b || !part) return SPZ_EINVAL;
+  RowWArgs W{};
+  W.n = 1;
+  W.j[0] = RowWJob{a, b, part, mblk, nblk, nblk, slices, 0};
+  W.groups = rows / (bf16 ? 16 : 8);
+  W.split = split;
+  hipError_t e = launch_row_wgrad(bf16 != 0, W, nullptr);
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e == hipErrorInvalidValue) return SPZ_EINVAL;
   return e == hipSuccess ? SPZ_OK : SPZ_EHIP;
 }
