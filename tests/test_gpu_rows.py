@@ -261,3 +261,17 @@ def test_float32_actions_on_either_path(obs_dim, hidden, created):
         assert np.array_equal(host, out.cpu().numpy()), n
         assert np.abs(host - ref[:n]).max() <= 1e-5, n
     g.close()
+
+
+@pytest.mark.parametrize("hidden", [(32, 32), (64, 64), (100, 70), (128, 128), (300, 200)])
+def test_read_params_gives_what_was_written(hidden):
+    """On both sides of the sizes that are copied directly, for every network and its moments."""
+    g = make_gpu(RAGGED_TD3.replace(name="io", hidden=hidden, batch=64))
+    rng = np.random.default_rng(2)
+    keys = ["actor", "critic1", "critic2", "tactor", "tcritic1", "tcritic2", "m_actor", "v_critic2"]
+    want = {k: rng.standard_normal(g.param_count(k)).astype(np.float32) for k in keys}
+    for k in keys:
+        g.write_params(k, want[k])
+    for k in keys:
+        assert np.array_equal(g.read_params(k), want[k]), k
+    g.close()
