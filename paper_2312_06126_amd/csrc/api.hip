@@ -1338,6 +1338,7 @@ hipError_t refresh_packed(spz_ctx* c, hipStream_t s) {
 }
 
 int setup_rows(spz_ctx* c) {
+  CK(prepare_rows(c->bf16));
   const size_t e = es(c);
   const int64_t Bp = c->rows_Bp;
   const int nh = (int)c->hidden.size(), nl = nh + 1;

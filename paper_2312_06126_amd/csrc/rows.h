@@ -81,7 +81,11 @@ struct RowArgs {
   const float* obs; float* act; int stochastic; uint32_t counter; int64_t row0;
 };
 
-// The caller's operations give no wave more than ROW_MAX_BLOCKS blocks.
+// Lets launch_rows use the whole LDS of a CU on the current device: once for each context, as
+// the attribute is the device's and a first launch may be one that is being captured.
+hipError_t prepare_rows(bool bf16);
+// The caller's operations give no wave more than ROW_MAX_BLOCKS blocks. Sampler actions where
+// obs is set, else halves of a step.
 hipError_t launch_rows(bool bf16, const RowArgs& g, size_t lds, hipStream_t s);
 
 // Weight gradients from packed images: job j gives part[slice][m block][n block][1024]

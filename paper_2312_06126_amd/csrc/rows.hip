@@ -13,8 +13,6 @@
 // 256 bf16 (376 inputs) at 16384 rows 420 -> 188 us; TD3 2 x 256 bf16 at 4096 rows 235 -> 60 us.
 #include "rows.h"
 
-#include <atomic>
-
 namespace spz {
 namespace {
 
@@ -1122,29 +1120,36 @@ __global__ void __launch_bounds__(256) k_row_adam(RowPArgs p) {
   }
 }
 
-template <typename T, int TM, bool ACT>
-hipError_t launch_rows_t(const RowArgs& g, size_t lds, hipStream_t s) {
-  static std::atomic<bool> ready{false};
-  if (!ready.load()) {
-    const hipError_t e = hipFuncSetAttribute((const void*)(k_rows<T, TM, ACT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+template <typename T, int TM>
+hipError_t prepare_rows_t() {
+  for (const void* f : {(const void*)(k_rows<T, TM, false>), (const void*)(k_rows<T, TM, true>)}) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
-    ready.store(true);
   }
-  (k_rows<T, TM, ACT>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
+  return hipSuccess;
+}
+
+template <typename T, int TM>
+hipError_t launch_rows_t(const RowArgs& g, size_t lds, hipStream_t s) {
+  if (g.obs) (k_rows<T, TM, true>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
+  else (k_rows<T, TM, false>)<<<g.tiles * g.parts, ROW_THREADS, lds, s>>>(g);
   return hipGetLastError();
 }
 
 }  // namespace
 
+hipError_t prepare_rows(bool bf16) {
+  if (!bf16) return prepare_rows_t<float, 1>();
+  const hipError_t e = prepare_rows_t<bf16_t, 1>();
+  return e == hipSuccess ? prepare_rows_t<bf16_t, 2>() : e;
+}
+
 hipError_t launch_rows(bool bf16, const RowArgs& g, size_t lds, hipStream_t s) {
   if (g.tiles < 1 || g.parts < 1 || g.parts > 2 || lds > 160 * 1024 || (g.tm != 1 && g.tm != 2) ||
       (!bf16 && g.tm != 1) || (int64_t)g.tiles * 32 * g.tm < g.B)
     return hipErrorInvalidValue;
-  const bool act = g.obs != nullptr;
-  if (!bf16) return act ? launch_rows_t<float, 1, true>(g, lds, s) : launch_rows_t<float, 1, false>(g, lds, s);
-  if (g.tm == 1) return act ? launch_rows_t<bf16_t, 1, true>(g, lds, s) : launch_rows_t<bf16_t, 1, false>(g, lds, s);
-  return act ? launch_rows_t<bf16_t, 2, true>(g, lds, s) : launch_rows_t<bf16_t, 2, false>(g, lds, s);
+  if (!bf16) return launch_rows_t<float, 1>(g, lds, s);
+  return g.tm == 1 ? launch_rows_t<bf16_t, 1>(g, lds, s) : launch_rows_t<bf16_t, 2>(g, lds, s);
 }
 
 hipError_t launch_row_wgrad(bool bf16, RowWArgs& w, hipStream_t s) {

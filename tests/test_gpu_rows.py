@@ -275,3 +275,23 @@ def test_read_params_gives_what_was_written(hidden):
     for k in keys:
         assert np.array_equal(g.read_params(k), want[k]), k
     g.close()
+
+
+@pytest.mark.parametrize("prec,hidden", [("fp32", (64, 64)), ("fp32", (400, 300)), ("bf16", (400, 300))])
+def test_first_action_call_in_a_captured_graph(prec, hidden):
+    """A new context's first launch is an action call that is being captured; its replays, with the
+    context's own eager calls between them, give the eager call's actions."""
+    w = RAGGED.replace(name="capture", prec=prec, hidden=hidden, batch=300)
+    obs = torch.randn(90, w.obs_dim, device="cuda")
+    act = torch.zeros(90, w.act_dim, device="cuda")
+    torch.cuda.synchronize()
+    g = make_gpu(w)
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        g.act_noalloc(obs.data_ptr(), 90, act.data_ptr(), True, 4, torch.cuda.current_stream())
+    for _ in range(3):
+        act.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(act.cpu().numpy(), g.act(obs.cpu().numpy(), True, 4))
+    g.close()
