@@ -47,7 +47,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #define LDS_AS __attribute__((address_space(3)))
 
@@ -327,18 +326,21 @@ __device__ inline void epi_pair(const GemmArgs& g, const f32x16& a0, const f32x1
       *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
     } else {
       // bf16 output. The epilogue is VALU-bound, so the per-value work is done on the
-      // rounded pairs where that is exact: ReLU (a bf16 is negative exactly when its
-      // bits are as int16; a rounded -0.0 becomes +0.0), the mask bits (masking before
-      // or after rounding gives the same bits), the mask bits out (after ReLU a value
-      // is > 0 exactly when its bits are nonzero); column sums and the row dot take
-      // both values of a pair with one v_dot2_f32_bf16 (products by 1, 0 are exact).
+      // rounded pairs where that is exact: the mask bits (masking before or after
+      // rounding gives the same bits), the mask bits out (after ReLU a value is > 0, or a
+      // NaN, exactly when its bits are nonzero); column sums and the row dot take
+      // both values of a pair with one v_dot2_f32_bf16 (products by 1, 0 are exact). The
+      // ReLU is an IEEE maximum of the sums: on the rounded pairs as int16 it made NaN
+      // zero, as the matrix instructions return negative ones (eight steps of 3 x 1024 at
+      // 131072 rows: 83.3 and 83.5 ms, runs of one side differ by 0.6).
       static_assert(!BITS_OUT || RELU, "mask bits out are taken of ReLU outputs");
       uint32_t w[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        w[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
         if constexpr (RELU)
-          w[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, w[e]), i16x2{0, 0}));
+          w[e] = pack_bf16x2(__builtin_elementwise_maximum(v[2 * e], 0.0f), __builtin_elementwise_maximum(v[2 * e + 1], 0.0f));
+        else
+          w[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
       }
       if constexpr (BITS) {
         const int wd = (int)(bits_lds[rl] >> (8 * (cgrp & 3)));
@@ -504,14 +506,15 @@ __device__ inline void epilogue_trans(const GemmArgs& g, const f32x16 (&acc)[BM 
     for (int j = 0; j < TN; ++j) {
       const int cb = wn * WCOLS + 32 * j;   // block's first column within the tile
       // w[2 q4 + t]: columns 8 q4 + 4 h + 2 t and + 1, rounded to bf16 as a stored C
-      // would be (ReLU on the rounded pair: a bf16 is negative exactly when its bits are
-      // as int16)
+      // would be (ReLU ahead of the rounding, for NaN)
       uint32_t w[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        w[e] = pack_bf16x2(acc[i][j][2 * e], acc[i][j][2 * e + 1]);
         if constexpr (RELU)
-          w[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, w[e]), i16x2{0, 0}));
+          w[e] = pack_bf16x2(__builtin_elementwise_maximum(acc[i][j][2 * e], 0.0f),
+                             __builtin_elementwise_maximum(acc[i][j][2 * e + 1], 0.0f));
+        else
+          w[e] = pack_bf16x2(acc[i][j][2 * e], acc[i][j][2 * e + 1]);
       }
       if constexpr (RDOT) {
         // Output-layer weights of the lane's 16 columns, packed bf16 pairs.

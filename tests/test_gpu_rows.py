@@ -114,7 +114,8 @@ def test_layered_actions_from_any_alignment(prec, obs_dim):
 
 @pytest.mark.parametrize("negative", [False, True], ids=["pos", "neg"])
 @pytest.mark.parametrize("prec,hidden,batch", [
-    ("bf16", (64,), 300), ("bf16", (200, 120), 300), ("bf16", (256, 256), 2000), ("fp32", (200, 120), 300)])
+    ("bf16", (64,), 300), ("bf16", (200, 120), 300), ("bf16", (256, 256), 2000), ("fp32", (200, 120), 300),
+    ("bf16", (256, 256), 300), ("bf16", (544, 100), 300), ("bf16", (1024,), 300), ("bf16", (512, 640), 3000)])
 def test_nan_reaches_actions_and_loss_record(prec, hidden, batch, negative):
     """A NaN of either sign, in an observation column or in a critic's first bias, makes the
     actions that depend on it NaN and sets the step's non-finite flag."""
