@@ -114,8 +114,6 @@ struct RowPBlk {
   int32_t ld;        // row stride of the weight; kind 1: columns of the partials
   int32_t job;       // kind 0: index into RowPArgs::j
   int32_t blk;       // kind 0: block index in the job's partials
-  int32_t fsteps, tsteps;
-  int32_t pad_;
   int64_t fwd, tr;   // element offsets of the block's fragments in the packed images (tr < 0: none);
                      // kind 1: of the columns' operand image (fwd < 0: none)
   const float* part; // kind 1, 2
