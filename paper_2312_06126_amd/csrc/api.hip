@@ -973,7 +973,8 @@ int row_vec(const spz_ctx* c) { return c->bf16 ? 8 : 4; }
 int row_ks(const spz_ctx* c) { return c->bf16 ? 16 : 8; }
 size_t align16z(size_t x) { return (x + 15) / 16 * 16; }
 
-// LDS layout of a tile of 32 tm rows with `nets` critics side by side; returns its bytes. The scratch area takes the partial blocks of products split over waves.
+// LDS layout of a tile of 32 tm rows with `nets` critics side by side; returns its bytes. The
+// scratch area takes the partial blocks of products split over waves.
 size_t row_layout(const spz_ctx* c, int tm, int nets, size_t scratch, RowArgs& g) {
   const int bm = 32 * tm, pa = c->net[0].L.back().out_p, nh = (int)c->hidden.size();
   const size_t e = es(c);
@@ -1286,8 +1287,8 @@ std::vector<RowWLayer> row_wlayers(const spz_ctx* c, int part) {
 }
 
 // Slices the batch of a launch's weight gradients is split into: a wave for each SIMD (1024),
-// two where a slice keeps 128 row groups (400-300 fp32, 32768 rows: 148 and 132 us; 2 x 256
-// fp32, 8192 rows, 64 and 32 groups: 33 and 36 us, as the slices have to be added up), and at
+// two where a slice keeps 128 row groups (400-300 fp32, 32768 rows: 345 and 270 us; 2 x 256
+// fp32, 8192 rows, 64 and 32 groups: 40 and 39 us, but 10 and 12 for adding the slices up), and at
 // least ROW_MIN_GROUPS row groups each.
 constexpr int ROW_SIMDS = 1024, ROW_LONG_GROUPS = 128, ROW_MIN_GROUPS = 4;
 int row_slices(int tiles, int groups) {
@@ -2824,9 +2825,8 @@ int spz_debug_read(spz_ctx* c, int32_t what, void* out, int64_t bytes) {
       break;
     }
     case SPZ_DBG_DACTION: {
-      // da1 [Bp, Ap] holds the whole gradient under the SAC row split, on the row-tile path
-      // (and for TD3);
-      // otherwise critic 2's part is in da2.
+      // da1 [Bp, Ap] holds the whole gradient under the SAC row split, on the row-tile path and
+      // for TD3; otherwise critic 2's part is in da2.
       const bool two = !c->td3 && !c->row_split && !c->last_rows;
       std::vector<float> d1((size_t)B * c->Ap), d2(two ? (size_t)B * c->Ap : 0);
       CK(hipMemcpy(d1.data(), c->da1, d1.size() * 4, hipMemcpyDeviceToHost));
