@@ -1867,15 +1867,18 @@ int setup_layers(spz_ctx* c) {
 }
 
 // The actor's forward buffers alone, for sampler-action calls layer by layer in a context whose
-// steps all take row tiles.
+// steps all take row tiles: made by the first such call.
 constexpr int64_t ACT_ROWS = 5120;
 int setup_act(spz_ctx* c) {
+  if (c->layers_Bp) return SPZ_OK;
   const size_t e = es(c);
-  const int64_t Bp = c->layers_Bp = std::min<int64_t>(c->Bp, ACT_ROWS);
+  const int64_t Bp = std::min<int64_t>(c->Bpmax, ACT_ROWS);
   CK(dalloc(c, &c->xsp, (size_t)Bp * c->Kc * e));
   CK(dalloc_t(c, &c->z, (size_t)Bp * c->net[0].L.back().out_p * 4));
   c->ha.assign(c->hidden.size(), nullptr);
   for (size_t l = 0; l < c->hidden.size(); ++l) CK(dalloc(c, &c->ha[l], (size_t)Bp * pad32(c->hidden[l]) * e));
+  CK(hipStreamSynchronize(nullptr));   // the clearing of what was allocated, ahead of work on the context's streams
+  c->layers_Bp = Bp;
   return SPZ_OK;
 }
 
@@ -1933,9 +1936,6 @@ int setup(spz_ctx* c) {
   }
   if (c->layers_ok) {
     const int rc = setup_layers(c);
-    if (rc) return rc;
-  } else if (!c->bf16 && row_act_macs(c) > ROW_ACT_SHORT) {
-    const int rc = setup_act(c);
     if (rc) return rc;
   }
   // one partial per 256-row block, or per wave of a row tile
@@ -2278,6 +2278,7 @@ int spz_act(spz_ctx* c, const float* obs, int64_t n, int32_t stochastic, uint32_
   // Chunks of at most the created batch (the actor workspaces' row count) and of the
   // observation staging area.
   const bool rows_act = row_act_on(c, n);
+  if (!rows_act && (rc = setup_act(c))) return rc;
   const int64_t chunk = std::min<int64_t>(rows_act ? c->Bpmax : c->layers_Bp, c->stage_rows) / 256 * 256;
   const int saveB = c->B, saveBp = c->Bp;
   const int pa = c->net[0].L.back().out_p;
