@@ -296,3 +296,41 @@ def test_first_action_call_in_a_captured_graph(prec, hidden):
         torch.cuda.synchronize()
         assert np.array_equal(act.cpu().numpy(), g.act(obs.cpu().numpy(), True, 4))
     g.close()
+
+
+@pytest.mark.parametrize("algo,obs_dim,act_dim,hidden,batch", [
+    ("sac", 376, 6, (400, 300), 257), ("sac", 300, 31, (480, 64, 512), 1000), ("sac", 376, 1, (416,), 33),
+    ("sac", 45, 3, (500, 330, 33), 1), ("sac", 7, 2, (480, 480, 480), 640)])
+def test_both_paths_agree(algo, obs_dim, act_dim, hidden, batch):
+    """float32 networks with a weight of more than 150000 elements (so the wide layers of the
+    fourth stand next to each other), whose small batches take row tiles on one stream and go
+    layer by layer from graphs on two: one step from the same state. Hidden layers and policy
+    heads sum in the same order on both paths: log-probabilities have the same bits. The critics'
+    one-column output and the gradients differ by the order of float32 sums over up to 1000
+    terms, about sqrt(1000) 2^-24 = 1.9e-6 of a tensor's norm at most (measured: 2.5e-7). Two
+    optimizer steps later an element whose gradient is of that size may have moved the other way
+    (measured: 7e-8 of the loss record's norm)."""
+    from paper_2312_06126_amd import Spz
+    w = RAGGED.replace(name="both", algo=algo, obs_dim=obs_dim, act_dim=act_dim, hidden=hidden, batch=batch)
+    out = []
+    for n_streams, graphs in ((1, False), (2, True)):
+        g = Spz(obs_dim, act_dim, hidden, batch, dict(w.hparams(), graphs=graphs), 1, n_streams=n_streams)
+        g.buffer_push(*synth.workload_rows(w, 0, 3000, 0))
+        if n_streams == 1:
+            g.profile_enable(True, 100)
+        g.update(1)
+        if n_streams == 1:
+            assert {s["name"] for s in g.profile_read()} == {"row_step", "row_wgrad", "row_adam"}
+        out.append({k: g.read_params("g_" + k).astype(np.float64) for k in ("actor", "critic1", "critic2", "log_alpha")})
+        out[-1].update(rec=g.read_losses(1, 1), q=g.debug_rows("q"), qpi=g.debug_rows("qpi"), logpi=g.debug_rows("logpi"))
+        g.update(2)
+        out[-1]["later"] = g.read_losses(2, 2)
+        g.profile_enable(True, 100)   # (eager while timing)
+        g.update(1)
+        assert ("row_step" in {s["name"] for s in g.profile_read()}) == (n_streams == 1)
+        g.close()
+    a, b = out
+    assert np.array_equal(a["logpi"], b["logpi"])
+    for k, tol in dict(q=2e-6, qpi=2e-6, rec=2e-6, actor=2e-6, critic1=2e-6, critic2=2e-6, log_alpha=2e-6,
+                       later=1e-5).items():
+        assert np.linalg.norm(a[k] - b[k]) <= tol * np.linalg.norm(b[k]), k
