@@ -521,20 +521,25 @@ def test_profile_only_times_one_kernel_and_keeps_results():
 
 
 def test_profile_stride_times_every_kth_step():
-    """With a profile stride of 3, only steps 3 and 6 of 7 carry timed launches."""
+    """With a profile stride of 3, only steps 3 and 6 of 7 carry timed launches. Records are told
+    apart by name and shape: some names have several shapes, and their order follows the times."""
+    def launches(g):
+        return {(s["name"], s["M"], s["N"], s["K"]): s["launches"] for s in g.profile_read()}
+
     w = FUSED_BF16
     g = make_gpu(w)
     g.buffer_push(*synth.workload_rows(w, 0, 5000, 0))
     g.profile_enable(True, 1000)
     g.profile_stride(3)
     g.update(7)
-    st = {s["name"]: s["launches"] for s in g.profile_read()}
+    st = launches(g)
     g.profile_enable(True, 1000)
     g.profile_stride(1)
     g.update(1)
-    one = {s["name"]: s["launches"] for s in g.profile_read()}
+    one = launches(g)
     g.close()
-    assert st["gather"] == 2 and st["finish"] == 2, st
+    for name in ("gather", "finish"):
+        assert [n for k, n in st.items() if k[0] == name] == [2], st
     assert st == {k: 2 * v for k, v in one.items()}, (st, one)
 
 
